@@ -225,7 +225,7 @@ struct hom4d {
     int red_blocks = 0;
     // slices
     int32_t* ix_dev = nullptr;   // 512 ints
-    double2* slice_dev = nullptr;// 256*256
+    double2* slice_dev = nullptr;// 256*256 slice values, 256*256 density matrix, kSliceScratch doubles
     double2* orb_dev = nullptr;  // 2 * nx*ny
     // state
     void* psi = nullptr;
@@ -573,39 +573,6 @@ int check_weights(const double* w, int n) {
     return HOM4D_OK;
 }
 
-// Eigenvalues of a real symmetric matrix (row-major, n x n, destroyed), cyclic Jacobi.
-void jacobi_eigenvalues(std::vector<double>& a, int n, std::vector<double>& ev) {
-    auto A = [&](int i, int j) -> double& { return a[(size_t)i * n + j]; };
-    double diag2 = 0.0;
-    for (int i = 0; i < n; ++i) diag2 += A(i, i) * A(i, i);
-    for (int sweep = 0; sweep < 100; ++sweep) {
-        double off = 0.0;
-        for (int p = 0; p < n; ++p)
-            for (int q = p + 1; q < n; ++q) off += A(p, q) * A(p, q);
-        if (off <= 1e-32 * std::max(diag2, 1e-300)) break;
-        for (int p = 0; p < n; ++p)
-            for (int q = p + 1; q < n; ++q) {
-                const double apq = A(p, q);
-                if (std::fabs(apq) < 1e-300) continue;
-                const double zeta = (A(q, q) - A(p, p)) / (2.0 * apq);
-                const double t = (zeta >= 0 ? 1.0 : -1.0) / (std::fabs(zeta) + std::sqrt(zeta * zeta + 1.0));
-                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < n; ++k) {
-                    const double akp = A(k, p), akq = A(k, q);
-                    A(k, p) = c * akp - s * akq;
-                    A(k, q) = s * akp + c * akq;
-                }
-                for (int k = 0; k < n; ++k) {
-                    const double apk = A(p, k), aqk = A(q, k);
-                    A(p, k) = c * apk - s * aqk;
-                    A(q, k) = s * apk + c * aqk;
-                }
-            }
-    }
-    ev.resize(n);
-    for (int i = 0; i < n; ++i) ev[i] = A(i, i);
-}
-
 int slice_checks(hom4d* h, const int32_t* ix1, int32_t n1, int32_t jy1, const int32_t* ix2, int32_t n2,
                  int32_t jy2) {
     const hom4d_cfg& c = h->cfg;
@@ -852,7 +819,7 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
         {(void**)&h->red_part, (size_t)h->red_blocks * 8 * sizeof(double)},
         {(void**)&h->red_out, 8 * sizeof(double)},
         {(void**)&h->ix_dev, 512 * sizeof(int32_t)},
-        {(void**)&h->slice_dev, 256 * 256 * sizeof(double2)},
+        {(void**)&h->slice_dev, 2 * 256 * 256 * sizeof(double2) + kSliceScratch * sizeof(double)},
         {(void**)&h->orb_dev, (size_t)2 * nx * ny * sizeof(double2)},
     };
     for (auto& a : allocs) {
@@ -1175,50 +1142,18 @@ int hom4d_entanglement(hom4d* h, const int32_t* ix1, int32_t n1, int32_t jy1, co
                        int32_t jy2, double* s_out) {
     if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
     if (!s_out) return fail(HOM4D_EINVAL, "s_out is NULL");
-    std::vector<double> phi;
-    int rc = gather(h, ix1, n1, jy1, ix2, n2, jy2, phi);
+    int rc = slice_checks(h, ix1, n1, jy1, ix2, n2, jy2);
     if (rc) return rc;
-    double nrm = 0.0;
-    for (double x : phi) nrm += x * x;
+    SliceIndex ix{};
+    for (int i = 0; i < n1; ++i) ix.a[i] = (uint8_t)ix1[i];
+    for (int i = 0; i < n2; ++i) ix.b[i] = (uint8_t)ix2[i];
+    double2* rho = h->slice_dev + 256 * 256;
+    HIP_TRY(launch_slice_entropy(h->psi, h->mixed, ix, n1, jy1, n2, jy2, h->cfg.nx, h->cfg.ny, h->slice_dev, rho,
+                                 reinterpret_cast<double*>(rho + 256 * 256), h->host_out, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    const double nrm = h->host_out[1];
     if (!(nrm > 0.0) || !std::isfinite(nrm)) return fail(HOM4D_ENONFINITE, "slice norm %g", nrm);
-    // rho over the smaller side: G = phi phi^dagger (n1 <= n2) or phi^dagger phi, Hermitian,
-    // embedded as the real symmetric [[Re, -Im], [Im, Re]] whose spectrum is G's, doubled.
-    const bool left = n1 <= n2;
-    const int m = left ? n1 : n2, kdim = left ? n2 : n1;
-    auto el = [&](int a, int b, double* re, double* im) {  // phi[a][b]
-        *re = phi[2 * ((size_t)a * n2 + b)] / std::sqrt(nrm);
-        *im = phi[2 * ((size_t)a * n2 + b) + 1] / std::sqrt(nrm);
-    };
-    std::vector<double> g((size_t)2 * m * 2 * m, 0.0);
-    for (int p = 0; p < m; ++p)
-        for (int q = 0; q < m; ++q) {
-            double re = 0.0, im = 0.0;
-            for (int k = 0; k < kdim; ++k) {
-                double ar, ai, br, bi;
-                if (left) {
-                    el(p, k, &ar, &ai);
-                    el(q, k, &br, &bi);
-                } else {
-                    el(k, p, &ar, &ai);
-                    el(k, q, &br, &bi);
-                    ai = -ai;
-                    bi = -bi;
-                }
-                re += ar * br + ai * bi;  // a * conj(b)
-                im += ai * br - ar * bi;
-            }
-            const int M = 2 * m;
-            g[(size_t)p * M + q] = re;
-            g[(size_t)(p + m) * M + (q + m)] = re;
-            g[(size_t)p * M + (q + m)] = -im;
-            g[(size_t)(p + m) * M + q] = im;
-        }
-    std::vector<double> ev;
-    jacobi_eigenvalues(g, 2 * m, ev);
-    double s = 0.0;
-    for (double lam : ev)
-        if (lam > 0.0) s -= lam * std::log(lam);
-    *s_out = 0.5 * s;
+    *s_out = h->host_out[0];
     return HOM4D_OK;
 }
 

@@ -153,6 +153,17 @@ hipError_t launch_reduce_parts(const double* part, int nparts, int width, double
 hipError_t launch_gather(const void* psi, bool mixed, const int32_t* ix1, int n1, int jy1,
                          const int32_t* ix2, int n2, int jy2, int nx, int ny, double2* out,
                          hipStream_t s);
+// Grid indices along x of a slice, by value in the kernel's arguments (nx <= 256).
+struct SliceIndex {
+    uint8_t a[256], b[256];
+};
+// Entropy of the n1 x n2 slice (slice_entropy.hip): out[0] = S, out[1] = sum |phi|^2
+// (device or pinned host memory).  phi: n1 n2 values, rho: min(n1, n2)^2 values,
+// scratch: kSliceScratch doubles.
+constexpr size_t kSliceScratch = 1024;
+hipError_t launch_slice_entropy(const void* psi, bool mixed, const SliceIndex& ix, int n1, int jy1, int n2, int jy2,
+                                int nx, int ny, double2* phi, double2* rho, double* scratch, double* out,
+                                hipStream_t s);
 hipError_t launch_marginal(const void* psi, bool mixed, int nxy, double* out, hipStream_t s);
 hipError_t launch_conditional(const void* psi, bool mixed, int nxy, int r2, double* out, hipStream_t s);
 hipError_t launch_c128_to_c64(const double2* in, float2* out, int64_t count, hipStream_t s);
