@@ -1,13 +1,12 @@
 // Hermitian (or real symmetric) tridiagonalisation by one workgroup with the
 // matrix in registers, and Sturm counts of the result (FP64).
 //
-// A 1024-thread block holds the matrix as a 32 x 32 thread grid with cyclic
-// ownership: thread (tr, tc) keeps elements (tr + 32 a, tc + 32 b), a, b < NB, so
-// every thread stays busy as the active window shrinks and NB = 4 carries 128 x
-// 128 complex values in 64 VGPRs of each of the 1024 threads; LDS only moves the
-// two vectors of a step.  (The matrix itself does not fit 160 KB of LDS at 128 x
-// 128 complex, and a pass over it in L2 per step is what bounds larger sizes,
-// tridiag_global below.)
+// A block of TR x 16 threads holds the matrix with cyclic ownership: thread
+// (tr, tc) keeps elements (tr + TR a, tc + 16 b), so every thread stays busy as the
+// active window shrinks; 512 threads carry 128 x 128 complex values in 128 VGPRs
+// each.  LDS only moves the two vectors of a step.  (The matrix itself does not fit
+// 160 KB of LDS at 128 x 128 complex, and a pass over it in L2 per step is what
+// bounds larger sizes, tridiag_global below.)
 //
 // Step s, with x the column s below the diagonal: the reflector
 // H = 1 - tau v v^H, v = x + (x_0 / |x_0|) ||x|| e_0, tau = 1 / (||x||^2 + |x_0| ||x||)
@@ -16,8 +15,16 @@
 // window becomes A - v w^H - w v^H.  Two barriers per step: one after the
 // column is in LDS, one after p is.  Each wavefront forms ||x||^2 and v^H p for
 // itself, from the same LDS values in the same order, so that every thread holds
-// the same bits and takes the same branches.  The chain of these steps, not the
-// arithmetic, bounds it: one block, 2 barriers and 2 wavefront reductions a step.
+// the same bits and takes the same branches.
+//
+// The chain of m - 1 steps on one CU bounds it.  What a step costs beyond its
+// 12 FP64 operations per element is work every wavefront repeats, so there are as few wavefronts
+// as the registers allow, the sums stay in DPP within 16 lanes (a row of the
+// thread grid is one DPP row), and square root and reciprocals are the hardware
+// estimates with two Newton steps.  128 x 128 complex: 278 us (421 us with 1024
+// threads, 32-lane shuffles and library square roots and divisions); 64 x 64: 92
+// us (152); 128 wave numbers' 96 x 96 real matrices, one per CU: 205 us with the
+// eigenvector.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -30,9 +37,8 @@ namespace hom4d_impl {
 namespace eig {
 using namespace hom4d_dev;
 
-constexpr int kThreads = 1024;  // 32 x 32 threads
-constexpr int kRegMax = 128;    // largest matrix held in registers (NB = 4)
-constexpr int kMax = 256;       // largest matrix
+constexpr int kRegMax = 128;  // largest matrix held in registers
+constexpr int kMax = 256;     // largest matrix
 // squared norms below this (of a column; the matrices are of order 1 or larger)
 // count as zero: dropping such a column changes an eigenvalue by less than 1e-140
 constexpr double kTiny2 = 1e-280;
@@ -67,38 +73,92 @@ __device__ __forceinline__ double2 msubr(double s, double2 a, double2 c) {
 __device__ __forceinline__ double redot(double a, double b) { return a * b; }
 __device__ __forceinline__ double redot(double2 a, double2 b) { return fma(a.x, b.x, a.y * b.y); }
 
-// x + (x of the lane that the DPP control names)
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double x) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-    return x + __hiloint2double(hi, lo);
+// 1 / sqrt(x) and 1 / x for normal x > 0: the hardware estimates and two Newton steps
+__device__ __forceinline__ double rsqrt_of(double x) {
+    const double h = 0.5 * x;
+    double r = __builtin_amdgcn_rsq(x);
+    r *= fma(-h * r, r, 1.5);
+    r *= fma(-h * r, r, 1.5);
+    return r;
 }
-// Sums over aligned groups of 32 lanes and over the wavefront, valid in every lane
-// (all lanes active): quad_perm, half-mirror and mirror within 16 lanes.
-__device__ __forceinline__ double sum32(double x) {
-    x = dpp_add<0xB1>(x);   // quad_perm 1 0 3 2
-    x = dpp_add<0x4E>(x);   // quad_perm 2 3 0 1
-    x = dpp_add<0x141>(x);  // row_half_mirror
-    x = dpp_add<0x140>(x);  // row_mirror
-    return x + __shfl_xor(x, 16, 64);
-}
-__device__ __forceinline__ double2 sum32(double2 x) { return make_double2(sum32(x.x), sum32(x.y)); }
-__device__ __forceinline__ double sum64(double x) {
-    x = sum32(x);
-    return x + __shfl_xor(x, 32, 64);
+__device__ __forceinline__ double rcp_of(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
 }
 
-// LDS of one tridiagonalisation.
+// the value of the lane that the DPP control names (within 16 lanes)
+constexpr int kXor15 = 0x140, kXor7 = 0x141, kXor3 = 0x1B, kXor1 = 0xB1;  // mirror, half mirror, quad_perm
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+template <int CTRL>
+__device__ __forceinline__ double2 dpp(double2 x) { return make_double2(dpp<CTRL>(x.x), dpp<CTRL>(x.y)); }
+__device__ __forceinline__ double add(double a, double b) { return a + b; }
+__device__ __forceinline__ double2 add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+
+__device__ __forceinline__ double lane_of(double x, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+// Sum over the wavefront, the same in every lane (all lanes active).
+__device__ __forceinline__ double sum64(double x) {
+    x += dpp<kXor15>(x);
+    x += dpp<kXor7>(x);
+    x += dpp<kXor3>(x);
+    x += dpp<kXor1>(x);
+    return (lane_of(x, 0) + lane_of(x, 16)) + (lane_of(x, 32) + lane_of(x, 48));
+}
+
+// Sums of C values each over 16 lanes, by halves: a stage sends the half of the
+// values that the partner keeps, until a lane holds one of the sums.
+template <int C, int CTRL, int BIT, class T>
+__device__ __forceinline__ void reduce_stage(T* acc, int lane, int& row) {
+    if constexpr (C > 1) {
+        constexpr int H = C / 2;
+        const bool up = (lane & BIT) != 0;
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            const T lo = acc[k], hi = acc[k + H];
+            acc[k] = add(up ? hi : lo, dpp<CTRL>(up ? lo : hi));
+        }
+        if (up) row += H;
+    } else {
+        acc[0] = add(acc[0], dpp<CTRL>(acc[0]));
+    }
+}
+// acc[0] becomes the sum of value `row` (returned) of the lane's group of 16; the
+// lanes whose bits below 16 / C are zero hold each sum once.
+template <int C, class T>
+__device__ __forceinline__ int reduce16(T* acc) {
+    static_assert((C & (C - 1)) == 0 && C <= 16, "a power of two");
+    const int lane = threadIdx.x & 15;
+    int row = 0;
+    reduce_stage<C, kXor15, 8>(acc, lane, row);
+    reduce_stage<(C > 2 ? C / 2 : 1), kXor7, 4>(acc, lane, row);
+    reduce_stage<(C > 4 ? C / 4 : 1), kXor3, 2>(acc, lane, row);
+    reduce_stage<(C > 8 ? C / 8 : 1), kXor1, 1>(acc, lane, row);
+    return row;
+}
+
+// LDS of one tridiagonalisation; cleared before the first step (clear()).
 template <class T>
 struct Work {
     T x[2][kMax];  // the current column / reflector (two steps alternate)
     T p[kMax];     // A v
+    __device__ __forceinline__ void clear() {
+        double* q = reinterpret_cast<double*>(this);
+        for (int i = threadIdx.x; i < (int)(sizeof(Work) / sizeof(double)); i += blockDim.x) q[i] = 0.0;
+        __syncthreads();
+    }
 };
 
-// The reflector of the column x (entries s + 1 .. m - 1, zeros at and below s):
-// entry s + 1 of v, tau, and the off-diagonal element it leaves.  NL: entries per
-// lane.  tau = 0: the column is already zero below s + 1.
+// The reflector of the column x (entries s + 1 .. m - 1, zeros elsewhere): entry
+// s + 1 of v, tau, and the off-diagonal element it leaves.  NL: entries per lane.
+// tau = 0: the column is already zero below s + 1.
 template <class T, int NL>
 struct Reflector {
     T v0, e;
@@ -106,6 +166,7 @@ struct Reflector {
     T mine[NL];  // v at entries lane + 64 l
     __device__ __forceinline__ Reflector(const T* x, int s) {
         const int lane = threadIdx.x & 63;
+        const T x0 = x[s + 1];
         double n2 = 0.0;
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
@@ -113,31 +174,31 @@ struct Reflector {
             if (lane + 64 * l != s + 1) n2 += abs2(mine[l]);
         }
         n2 = sum64(n2);
-        const T x0 = x[s + 1];
-        const double a2 = abs2(x0);
         if (!(n2 > kTiny2)) {
             tau = 0.0;
             v0 = zero_of(x0);
             e = x0;
             return;
         }
-        const double nrm = sqrt(n2 + a2), a = sqrt(a2);
+        const double a2 = abs2(x0), t2 = n2 + a2;
+        const double nrm = t2 * rsqrt_of(t2);
+        double a;
         if constexpr (std::is_same<T, double>::value) {
-            const double sg = x0 < 0.0 ? -1.0 : 1.0;
-            v0 = x0 + sg * nrm;
-            e = -sg * nrm;
+            a = fabs(x0);
+            e = x0 < 0.0 ? nrm : -nrm;
+            v0 = x0 - e;
         } else {
-            T ph;  // x0 / |x0|
+            T ph = make_double2(1.0, 0.0);  // x0 / |x0|
+            a = 0.0;
             if (a2 > kTiny2) {
-                ph = scaled(x0, 1.0 / a);
-            } else {
-                ph = zero_of(x0);
-                ph.x = 1.0;
+                const double r = rsqrt_of(a2);
+                a = a2 * r;
+                ph = scaled(x0, r);
             }
-            v0 = make_double2(fma(ph.x, nrm, x0.x), fma(ph.y, nrm, x0.y));
             e = scaled(ph, -nrm);
+            v0 = make_double2(x0.x - e.x, x0.y - e.y);
         }
-        tau = 1.0 / (n2 + a2 + a * nrm);
+        tau = rcp_of(fma(a, nrm, t2));
 #pragma unroll
         for (int l = 0; l < NL; ++l)
             if (lane + 64 * l == s + 1) mine[l] = v0;
@@ -152,106 +213,102 @@ struct Reflector {
     }
 };
 
-// Tridiagonalise the m x m matrix of the registers (elements at and past m zero;
-// m <= 32 NB): d[0 .. m-1] gets the diagonal, step(s, e, tau, v) is called by every
-// thread for each column s = 0 .. m - 2 with the off-diagonal element e, and with
-// the reflector in LDS where tau != 0 (v[s + 1 ..], entries at and below s zero).
-template <class T, int NB, class Step>
-__device__ __forceinline__ void tridiag_regs(T (&A)[NB][NB], int m, Work<T>& wk, double* d, Step step) {
-    constexpr int NL = (NB + 1) / 2;  // entries per lane of a vector of 32 NB
-    const int tid = threadIdx.x, tr = tid >> 5, tc = tid & 31;
-    sfor<0, NB>([&](auto cbc) {
-        constexpr int CB = decltype(cbc)::value;
-        const int s1 = m < 32 * (CB + 1) ? m : 32 * (CB + 1);
-        for (int s = 32 * CB; s < s1; ++s) {
+// Tridiagonalise the m x m matrix of the registers (m <= N = TR RA = 16 CB; elements
+// at and past m zero): d[0 .. m-1] gets the diagonal; step(s, h, x) is called by
+// every thread for each column s = 0 .. m - 2 with its Reflector and the column in
+// LDS (the reflector's entries past s + 1).
+template <class T, int TR, int RA, int CB, class Step>
+__device__ __forceinline__ void tridiag_regs(T (&A)[RA][CB], int m, Work<T>& wk, double* d, Step step) {
+    static_assert(TR * RA == 16 * CB, "a square matrix");
+    constexpr int N = TR * RA, NL = (N + 63) / 64;
+    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
+    sfor<0, CB>([&](auto cbc) {
+        constexpr int C0 = decltype(cbc)::value, A0 = 16 * C0 / TR;  // first active blocks
+        const int s1 = m < 16 * (C0 + 1) ? m : 16 * (C0 + 1);
+        for (int s = 16 * C0; s < s1; ++s) {
             T* x = wk.x[s & 1];
-            if (tc == (s & 31)) {
+            if (tc == (s & 15)) {
 #pragma unroll
-                for (int a = 0; a < NB; ++a) {
-                    const int i = tr + 32 * a;
-                    const T v = A[a][CB];
+                for (int a = 0; a < RA; ++a) {
+                    const int i = tr + TR * a;
+                    const T v = A[a][C0];
                     if (i == s) d[s] = real_of(v);
                     x[i] = i > s ? v : zero_of(v);
                 }
-                // a vector of 32 entries (NB = 1) is read 64 wide
-                if constexpr (NB % 2 == 1) x[32 * NB + tr] = zero_of(A[0][0]);
             }
             __syncthreads();
             if (s == m - 1) break;
             const Reflector<T, NL> h(x, s);
             if (h.tau != 0.0) {
-                T vc[NB];
+                {
+                    T acc[RA];
 #pragma unroll
-                for (int b = CB; b < NB; ++b) {
-                    const int j = tc + 32 * b;
-                    vc[b] = j == s + 1 ? h.v0 : x[j];
-                }
+                    for (int a = 0; a < RA; ++a) acc[a] = zero_of(h.v0);
 #pragma unroll
-                for (int a = CB; a < NB; ++a) {
-                    T acc = zero_of(vc[CB]);
+                    for (int b = C0; b < CB; ++b) {
+                        const int j = tc + 16 * b;
+                        const T vj = j == s + 1 ? h.v0 : x[j];
 #pragma unroll
-                    for (int b = CB; b < NB; ++b) acc = madd(A[a][b], vc[b], acc);
-                    acc = sum32(acc);
-                    if (tc == 0) wk.p[tr + 32 * a] = acc;
-                }
-                if (NB % 2 == 1 && tid < 32) wk.p[32 * NB + tid] = zero_of(vc[CB]);
-                // rows below the window's first block hold no part of v
-                if constexpr (CB > 0) {
-                    if (tid < 32 * CB) wk.p[tid] = zero_of(vc[CB]);
+                        for (int a = A0; a < RA; ++a) acc[a] = madd(A[a][b], vj, acc[a]);
+                    }
+                    const int row = reduce16<RA>(acc);
+                    if ((tc & (16 / RA - 1)) == 0) wk.p[tr + TR * row] = acc[0];
                 }
                 __syncthreads();
                 const double half = 0.5 * h.tau * h.tau * h.dot(wk.p);
-                T wc[NB];
+                T vr[RA], wr[RA];
 #pragma unroll
-                for (int b = CB; b < NB; ++b) wc[b] = msubr(half, vc[b], scaled(wk.p[tc + 32 * b], h.tau));
+                for (int a = A0; a < RA; ++a) {
+                    const int i = tr + TR * a;
+                    vr[a] = i == s + 1 ? h.v0 : x[i];
+                    wr[a] = msubr(half, vr[a], scaled(wk.p[i], h.tau));
+                }
 #pragma unroll
-                for (int a = CB; a < NB; ++a) {
-                    const int i = tr + 32 * a;
-                    const T vr = i == s + 1 ? h.v0 : x[i];
-                    const T wr = msubr(half, vr, scaled(wk.p[i], h.tau));
+                for (int b = C0; b < CB; ++b) {
+                    const int j = tc + 16 * b;
+                    const T vj = j == s + 1 ? h.v0 : x[j];
+                    const T wj = msubr(half, vj, scaled(wk.p[j], h.tau));
 #pragma unroll
-                    for (int b = CB; b < NB; ++b) A[a][b] = msubc(wr, vc[b], msubc(vr, wc[b], A[a][b]));
+                    for (int a = A0; a < RA; ++a) A[a][b] = msubc(wr[a], vj, msubc(vr[a], wj, A[a][b]));
                 }
             }
-            step(s, h.e, h.tau, h.v0, x);
+            step(s, h, x);
         }
     });
 }
 
 // The first n_steps steps on an m x m matrix in global memory (row-major, both
 // halves kept; m <= kMax), for matrices past the registers: each step reads the
-// window for p = A v and reads and writes it for the update.
-template <class T, class Step>
+// window for p = A v and reads and writes it for the update.  TR: threads / 16.
+template <class T, int TR, class Step>
 __device__ __forceinline__ void tridiag_global(T* A, int m, int n_steps, Work<T>& wk, double* d, Step step) {
     constexpr int NL = kMax / 64;
-    const int tid = threadIdx.x, tr = tid >> 5, tc = tid & 31;
+    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
     for (int s = 0; s < n_steps; ++s) {
         T* x = wk.x[s & 1];
-        if (tid < kMax) {
+        for (int i = tid; i < kMax; i += 16 * TR) {
             // column s as the conjugate of row s
             T v = zero_of(wk.p[0]);
-            if (tid >= s && tid < m) v = conj_of(A[(size_t)s * m + tid]);
-            if (tid == s) d[s] = real_of(v);
-            x[tid] = tid > s ? v : zero_of(v);
+            if (i >= s && i < m) v = conj_of(A[(size_t)s * m + i]);
+            if (i == s) d[s] = real_of(v);
+            x[i] = i > s ? v : zero_of(v);
         }
         __syncthreads();
         const Reflector<T, NL> h(x, s);
         if (h.tau != 0.0) {
-            const int b0 = s >> 5;
-            for (int i = tr + 32 * b0; i < m; i += 32) {
+            const int j0 = s & ~15, i0 = s / TR * TR;
+            for (int i = tr + i0; i < m; i += TR) {
                 T acc = zero_of(h.v0);
-                for (int j = tc + 32 * b0; j < m; j += 32) acc = madd(A[(size_t)i * m + j], j == s + 1 ? h.v0 : x[j], acc);
-                acc = sum32(acc);
+                for (int j = tc + j0; j < m; j += 16) acc = madd(A[(size_t)i * m + j], j == s + 1 ? h.v0 : x[j], acc);
+                reduce16<1>(&acc);
                 if (tc == 0) wk.p[i] = acc;
             }
-            // p outside the window meets zeros of v only
-            if (tid < 32 * b0 || (tid >= m && tid < kMax)) wk.p[tid] = zero_of(h.v0);
             __syncthreads();
             const double half = 0.5 * h.tau * h.tau * h.dot(wk.p);
-            for (int i = tr + 32 * b0; i < m; i += 32) {
+            for (int i = tr + i0; i < m; i += TR) {
                 const T vr = i == s + 1 ? h.v0 : x[i];
                 const T wr = msubr(half, vr, scaled(wk.p[i], h.tau));
-                for (int j = tc + 32 * b0; j < m; j += 32) {
+                for (int j = tc + j0; j < m; j += 16) {
                     const T vj = j == s + 1 ? h.v0 : x[j];
                     const T wj = msubr(half, vj, scaled(wk.p[j], h.tau));
                     T* q = A + (size_t)i * m + j;
@@ -259,56 +316,57 @@ __device__ __forceinline__ void tridiag_global(T* A, int m, int n_steps, Work<T>
                 }
             }
         }
-        step(s, h.e, h.tau, h.v0, x);
+        step(s, h, x);
         __syncthreads();  // the next column is read by other threads
     }
 }
 
-// Eigenvalues below x of the tridiagonal matrix with diagonal d and squared
-// off-diagonals e2: sign changes of the leading minors p_{i+1} = (d_i - x) p_i -
-// e2_{i-1} p_{i-1} (Givens), rescaled every four rows.  The recurrence takes two
-// dependent FP64 operations a row where the quotient form takes a division.
-__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int m, double x) {
-    double p0 = 1.0, p1 = d[0] - x;
-    int count = p1 < 0.0 ? 1 : 0;
-    bool neg = p1 < 0.0;
-    for (int i = 1; i < m; i += 4) {
-        const int n = fmax(fabs(p0), fabs(p1)) > 0.0 ? -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1))) : 0;
+// A tridiagonal matrix as Sturm counts read it: entry i holds the diagonal d_i and
+// the squared off-diagonal e2_{i-1} before it (at least kTiny2: a vanishing coupling
+// still separates the minors' signs), padded to whole groups of eight with rows
+// above every eigenvalue.
+constexpr int kSturmRows = (kMax + 7) / 8 * 8;
+__device__ __forceinline__ double2 sturm_row(double d, double e2) { return make_double2(d, fmax(e2, kTiny2)); }
+__device__ __forceinline__ double2 sturm_pad(double above) { return make_double2(above, kTiny2); }
+
+// Eigenvalues below x: sign changes of the leading minors p_{i+1} = (d_i - x) p_i -
+// e2_{i-1} p_{i-1} (Givens), rescaled every eight rows.  One dependent FP64
+// operation a row, where the quotient form takes a division.  A zero minor counts
+// one change in all whatever its sign, since the next one is opposite to its predecessor.
+__device__ __forceinline__ int sturm_count(const double2* t, int m, double x) {
+    double p0 = 0.0, p1 = 1.0;
+    int count = 0;
+    for (int i = 0; i < m; i += 8) {
+        double2 r[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) r[q] = t[i + q];
+        const int n = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
         p0 = ldexp(p0, n);
         p1 = ldexp(p1, n);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (i + q < m) {
-                // a vanishing coupling still separates the minors' signs
-                const double p2 = fma(d[i + q] - x, p1, -fmax(e2[i + q - 1], kTiny2) * p0);
-                // a zero minor takes the sign opposite to its predecessor's
-                const bool n2 = p2 < 0.0 || (p2 == 0.0 && !neg);
-                count += n2 != neg ? 1 : 0;
-                neg = n2;
-                p0 = p1;
-                p1 = p2;
-            }
+        for (int q = 0; q < 8; ++q) {
+            const double p2 = fma(r[q].x - x, p1, -r[q].y * p0);
+            count += (unsigned)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31;
+            p0 = p1;
+            p1 = p2;
         }
     }
     return count;
 }
 
-// The k-th smallest eigenvalue (k from 0) by a wavefront, every lane the same
-// value: 64 points a round split [lo, hi] in 65 parts.
-__device__ __forceinline__ double sturm_select(const double* d, const double* e2, int m, int k, double lo, double hi,
-                                               int rounds) {
+// Bracket [lo, hi] of the k-th smallest eigenvalue (k from 0) by a wavefront, every
+// lane the same: 64 points a round split it in 65 parts.
+__device__ __forceinline__ void sturm_select(const double2* t, int m, int k, double& lo, double& hi, int rounds) {
     const int lane = threadIdx.x & 63;
     for (int r = 0; r < rounds; ++r) {
         const double h = (hi - lo) * (1.0 / 65.0);
         const double x = fma((double)(lane + 1), h, lo);
-        const bool above = sturm_count(d, e2, m, x) > k;  // the eigenvalue lies below x
-        const unsigned long long b = __ballot(above);
+        const unsigned long long b = __ballot(sturm_count(t, m, x) > k);  // it lies below x
         const int first = b ? __ffsll((long long)b) - 1 : 64;
-        const double nlo = fma((double)first, h, lo);
-        if (first < 64) hi = fma((double)(first + 1), h, lo);
-        lo = nlo;
+        const double base = lo;
+        lo = fma((double)first, h, base);
+        if (first < 64) hi = fma((double)(first + 1), h, base);
     }
-    return 0.5 * (lo + hi);
 }
 
 }  // namespace eig

@@ -6,7 +6,8 @@
 // Gram matrix, its tridiagonalisation by one workgroup with the matrix in
 // registers (eigen_regs.hpp), the eigenvalues by bisection, a wavefront each, and
 // the sum.  All arithmetic is FP64, sums in a fixed order.  Only (S, norm) leave
-// the GPU.  On the host, with the 2m x 2m real embedding and cyclic Jacobi, one call took
+// the GPU.  Measured: 4 + 12 + 278 + 26 + 4 us at m = 128, 4 + 8 + 92 + 14 + 4 us at
+// m = 64, the tridiagonalisation's chain of steps bounding both.  On the host, with the 2m x 2m real embedding and cyclic Jacobi, one call took
 // 15 ms at m = 64 and 0.7-1.0 s at m = 128.
 #include "axis_pass.hpp"
 #include "eigen_regs.hpp"
@@ -85,48 +86,48 @@ __global__ void __launch_bounds__(256) k_slice_gram(const double2* a, int m, int
     }
 }
 
-// One block: diagonal d and squared off-diagonals e2 of the tridiagonal form of
-// rho.  NB: 32 x 32 register blocks per side; with more than eig::kRegMax rows the
-// first steps run on the matrix in memory.
-template <int NB>
-__global__ void __launch_bounds__(eig::kThreads) k_slice_tridiag(double2* rho, int m, double* d, double* e2) {
+// One block of TR x 16 threads: diagonal d and squared off-diagonals e2 of the
+// tridiagonal form of rho.  With more than eig::kRegMax rows the first steps run
+// on the matrix in memory.
+template <int TR, int RA, int CB>
+__global__ void __launch_bounds__(16 * TR) k_slice_tridiag(double2* rho, int m, double* d, double* e2) {
     __shared__ eig::Work<double2> wk;
-    const int tid = threadIdx.x, tr = tid >> 5, tc = tid & 31;
+    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
     int s0 = 0;
-    auto keep = [&](int s, double2 e, double, double2, const double2*) {
-        if (tid == 0) e2[s0 + s] = eig::abs2(e);
+    auto keep = [&](int s, const auto& h, const double2*) {
+        if (tid == 0) e2[s0 + s] = eig::abs2(h.e);
     };
-    if constexpr (32 * NB == eig::kRegMax) {
+    wk.clear();
+    if constexpr (TR * RA == eig::kRegMax) {
         if (m > eig::kRegMax) {
-            eig::tridiag_global(rho, m, m - eig::kRegMax, wk, d, keep);
+            eig::tridiag_global<double2, TR>(rho, m, m - eig::kRegMax, wk, d, keep);
             s0 = m - eig::kRegMax;
+            wk.clear();
         }
     }
-    double2 A[NB][NB];
+    double2 A[RA][CB];
 #pragma unroll
-    for (int a = 0; a < NB; ++a)
+    for (int a = 0; a < RA; ++a)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int i = s0 + tr + 32 * a, j = s0 + tc + 32 * b;
+        for (int b = 0; b < CB; ++b) {
+            const int i = s0 + tr + TR * a, j = s0 + tc + 16 * b;
             A[a][b] = i < m && j < m ? rho[(size_t)i * m + j] : make_double2(0.0, 0.0);
         }
-    eig::tridiag_regs<double2, NB>(A, m - s0, wk, d + s0, keep);
+    eig::tridiag_regs<double2, TR, RA, CB>(A, m - s0, wk, d + s0, keep);
 }
 
 // Eigenvalue k per wavefront.  rho is positive with unit trace, so they lie in
 // [0, 1] up to rounding; ten rounds of 65 leave an interval below 1e-18.
 __global__ void __launch_bounds__(256) k_slice_spectrum(const double* d, const double* e2, int m, double* lam) {
-    __shared__ double sd[eig::kMax], se[eig::kMax];
+    __shared__ double2 t[eig::kSturmRows];
     const int tid = threadIdx.x;
-    if (tid < m) {
-        sd[tid] = d[tid];
-        se[tid] = tid < m - 1 ? e2[tid] : 0.0;
-    }
+    t[tid] = tid < m ? eig::sturm_row(d[tid], tid > 0 ? e2[tid - 1] : 0.0) : eig::sturm_pad(3.0);
     __syncthreads();
     const int k = blockIdx.x * 4 + (tid >> 6);
     if (k >= m) return;
-    const double x = eig::sturm_select(sd, se, m, k, -1e-9, 1.0 + 1e-9, 10);
-    if ((tid & 63) == 0) lam[k] = x;
+    double lo = -1e-9, hi = 1.0 + 1e-9;
+    eig::sturm_select(t, m, k, lo, hi, 10);
+    if ((tid & 63) == 0) lam[k] = 0.5 * (lo + hi);
 }
 
 __global__ void k_slice_entropy(const double* lam, int m, const double* part, int nparts, double* out) {
@@ -162,9 +163,13 @@ hipError_t launch_slice_entropy(const void* psi, bool mixed, const SliceIndex& i
                            jy1, jy2, nx, ny, phi, part);
     const int nt = (m + kTile - 1) / kTile;
     hipLaunchKernelGGL(k_slice_gram, dim3(nt, nt), dim3(256), 0, s, phi, m, kd, part, nparts, rho);
-    // the fewest register blocks that hold the matrix: a step's work goes with their square
-    auto tri = m <= 32 ? k_slice_tridiag<1> : m <= 64 ? k_slice_tridiag<2> : k_slice_tridiag<4>;
-    hipLaunchKernelGGL(tri, dim3(1), dim3(eig::kThreads), 0, s, rho, m, d, e2);
+    // the smallest register form that holds the matrix, on as few wavefronts as hold it
+    if (m <= 32)
+        hipLaunchKernelGGL((k_slice_tridiag<16, 2, 2>), dim3(1), dim3(256), 0, s, rho, m, d, e2);
+    else if (m <= 64)
+        hipLaunchKernelGGL((k_slice_tridiag<16, 4, 4>), dim3(1), dim3(256), 0, s, rho, m, d, e2);
+    else
+        hipLaunchKernelGGL((k_slice_tridiag<32, 4, 8>), dim3(1), dim3(512), 0, s, rho, m, d, e2);
     hipLaunchKernelGGL(k_slice_spectrum, dim3((m + 3) / 4), dim3(256), 0, s, d, e2, m, lam);
     hipLaunchKernelGGL(k_slice_entropy, dim3(1), dim3(256), 0, s, lam, m, part, nparts, out);
     return hipGetLastError();
