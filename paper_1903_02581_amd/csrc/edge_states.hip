@@ -7,242 +7,344 @@
 //     H(k) = kappa [ -d^2/dy^2 + (k - y eB/hbar)^2 ] + v(y),
 // with the second derivative spectral on the periodic y grid: the circulant
 // matrix c[(i - j) mod ny], c[d] = (kappa / ny) sum_m ky_m^2 cos(2 pi m d / ny),
-// whose first row the host computes.  k_edge_jacobi diagonalises H(k) for every
-// grid k (one workgroup per k) by the cyclic Jacobi method with the round-robin
-// ordering of disjoint index pairs: each of the ny - 1 steps of a sweep rotates
-// ny / 2 disjoint (p, q) planes at once, the angles all taken from the matrix
-// before the step, then applied to the rows (J^T A), then to the columns (A J)
-// and to the accumulated eigenvectors (V J).  Sweeps repeat until the
-// off-diagonal part stops shrinking at rounding level.  The lowest diagonal
-// entry and its column of V are the edge state, its sign fixed so that the
-// largest-magnitude component is positive.
+// whose first row the host computes.  k_edge_state finds the lowest eigenpair of
+// H(k) for every grid k, one workgroup per k: Householder tridiagonalisation with
+// the matrix in registers (eigen_regs.hpp), bisection from Sturm counts, the
+// tridiagonal eigenvector from a twisted factorisation (Fernando; Parlett and
+// Dhillon), the reflectors applied to it in reverse, and its sign fixed so that the
+// largest-magnitude component is positive.  Only the lowest pair is wanted, so
+// this takes one reduction where the full Jacobi diagonalisation it replaces took
+// 7-9 sweeps of 3 barriers per rotation step over a matrix in L2: 20.4 -> 0.21 ms
+// at nx = 128, ny = 96.
 //
 // k_edge_sum forms psi(x_i, y_j) = sum_m exp(-sigma^2 (k_m - k0)^2)
 // exp(i k_m (x_i - xc)) phi_m(y_j) with the m sum in grid order, where k0 is the
 // grid wave number (on the requested side: k > 0 for the top edge, k < 0 for the
 // bottom) whose edge-state energy is closest to hbar omega_c / 2 + e_above;
-// k_edge_scale normalises it on the grid.  All arithmetic is FP64; the matrices
-// live in a device work buffer of 2 nx ny^2 doubles.
+// k_edge_scale normalises it on the grid.  All arithmetic is FP64.
+#include "axis_pass.hpp"
+#include "eigen_regs.hpp"
 #include "hom4d_internal.hpp"
 
 namespace hom4d_impl {
 namespace {
 
-constexpr int kEdgeThreads = 256;
-constexpr int kEdgeMaxSweeps = 40;
+using namespace dev;
 
-// sums of two values over the block, valid in every thread
-__device__ void block_sum2(double& a, double& b, double* red) {
-    const int tid = threadIdx.x, nw = blockDim.x / 64;
+constexpr int kThreads = 256;
+constexpr int kTR = kThreads / 16;
+
+// Reflector s of an m x m reduction: entries s + 1 .. m - 1, packed.
+__device__ __forceinline__ int reflector_at(int s, int m) { return s * (m - 1) - s * (s - 1) / 2 - (s + 1); }
+
+// One workgroup per wave number.  MEM: ny > eig::kRegMax, the matrix and the
+// reflectors in global memory (work: ny^2, then ny (ny - 1) / 2 doubles per k);
+// otherwise the matrix is in registers and the reflectors in LDS.
+template <int RA, int CB, bool MEM>
+__global__ void __launch_bounds__(kThreads) k_edge_state(EdgeArgs g) {
+    __shared__ eig::Work<double> wk;
+    __shared__ double2 t[eig::kSturmRows];                     // Sturm rows
+    __shared__ double circ[eig::kMax], d[eig::kMax], e[eig::kMax], tau[eig::kMax];
+    __shared__ double piv[2][eig::kMax], z[eig::kMax];
+    extern __shared__ double lds_refl[];
+    const int m = g.ny, tid = threadIdx.x, lane = tid & 63, tr = tid >> 4, tc = tid & 15;
+    const double k = g.kx[blockIdx.x];
+    double* A = MEM ? g.work + (size_t)blockIdx.x * ((size_t)m * m + (size_t)m * (m - 1) / 2) : nullptr;
+    double* refl = MEM ? A + (size_t)m * m : lds_refl;
+    if (tid < m) circ[tid] = g.circ[tid];
+    wk.clear();
+
+    auto element = [&](int i, int j) {
+        double a = circ[i >= j ? i - j : i - j + m];
+        if (i == j) {
+            const double u = k - (g.y0 + g.dy * i) * g.inv_lb2;
+            a += g.kappa * u * u + g.vcol[i];
+        }
+        return a;
+    };
+    int s0 = 0;
+    auto keep = [&](int sl, const auto& h, const double* x) {
+        const int s = s0 + sl, i = s0 + tid;
+        if (h.tau != 0.0 && tid > sl && i < m) refl[reflector_at(s, m) + i] = tid == sl + 1 ? h.v0 : x[tid];
+        if (tid == 0) {
+            e[s] = h.e;
+            tau[s] = h.tau;
+        }
+    };
+    if constexpr (MEM) {
+        for (int q = tid; q < m * m; q += kThreads) A[q] = element(q / m, q % m);
+        __syncthreads();
+        eig::tridiag_global<double, kTR>(A, m, m - eig::kRegMax, wk, d, keep);
+        s0 = m - eig::kRegMax;
+        wk.clear();
+    }
+    {
+        double M[RA][CB];
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                const int i = s0 + tr + kTR * a, j = s0 + tc + 16 * b;
+                M[a][b] = 0.0;
+                if (i < m && j < m) M[a][b] = MEM ? A[(size_t)i * m + j] : element(i, j);
+            }
+        eig::tridiag_regs<double, kTR, RA, CB>(M, m - s0, wk, d + s0, keep);
+    }
+    __syncthreads();
+
+    // lowest eigenvalue: between the Gershgorin bound and the smallest diagonal entry
+    double lo = 1e300, hi = 1e300, top = -1e300;
+    for (int i = lane; i < m; i += 64) {
+        const double r = (i > 0 ? fabs(e[i - 1]) : 0.0) + (i < m - 1 ? fabs(e[i]) : 0.0);
+        lo = fmin(lo, d[i] - r);
+        hi = fmin(hi, d[i]);
+        top = fmax(top, d[i] + r);
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        a += __shfl_xor(a, o, 64);
-        b += __shfl_xor(b, o, 64);
+        lo = fmin(lo, __shfl_xor(lo, o, 64));
+        hi = fmin(hi, __shfl_xor(hi, o, 64));
+        top = fmax(top, __shfl_xor(top, o, 64));
     }
+    const double span = top - lo;
+    t[tid] = tid < m ? eig::sturm_row(d[tid], tid > 0 ? e[tid - 1] * e[tid - 1] : 0.0) : eig::sturm_pad(top + span + 1.0);
     __syncthreads();
-    if ((tid & 63) == 0) {
-        red[2 * (tid >> 6)] = a;
-        red[2 * (tid >> 6) + 1] = b;
+    // (every wavefront the same rounds, so that they stay together for the barriers below)
+    lo -= 1e-15 * span;
+    eig::sturm_select(t, m, 0, lo, hi, 10);
+
+    // Eigenvector of the tridiagonal matrix at a shift l: the pivots of the
+    // factorisations from the top (lane 0) and from the bottom (lane 1), joined at
+    // the row where they leave the smallest residual gamma.  From the lower end of
+    // the bracket T - l is positive definite; a second pass at the Rayleigh-corrected
+    // shift takes out the bracket's rounding.
+    double shift = lo;
+    const double tiny = 1e-30 * span;
+    for (int pass = 0; pass < 2; ++pass) {
+        if (tid < 2) {
+            double p = 1.0, c2 = 0.0;
+            for (int q = 0; q < m; ++q) {
+                const int i = tid == 0 ? q : m - 1 - q;
+                p = fma(-c2, eig::rcp_of(p), d[i] - shift);
+                if (fabs(p) < tiny) p = p < 0.0 ? -tiny : tiny;
+                piv[tid][i] = p;
+                if (q < m - 1) {
+                    const double c = e[tid == 0 ? i : i - 1];
+                    c2 = c * c;
+                }
+            }
+        }
+        __syncthreads();
+        double best = 1e300;
+        int at = 0;
+        for (int i = lane; i < m; i += 64) {
+            const double gm = fabs(piv[0][i] + piv[1][i] - (d[i] - shift));
+            if (gm < best) {
+                best = gm;
+                at = i;
+            }
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            const double ob = __shfl_xor(best, o, 64);
+            const int oa = __shfl_xor(at, o, 64);
+            if (ob < best || (ob == best && oa < at)) {
+                best = ob;
+                at = oa;
+            }
+        }
+        const double gamma = piv[0][at] + piv[1][at] - (d[at] - shift);
+        __syncthreads();
+        // the ratio of each row to its neighbour on the side of row `at`
+        if (tid < m) z[tid] = tid < at ? -e[tid] * eig::rcp_of(piv[0][tid]) : tid > at ? -e[tid - 1] * eig::rcp_of(piv[1][tid]) : 1.0;
+        __syncthreads();
+        if (tid == 0) {
+            double p = 1.0;
+            for (int i = at - 1; i >= 0; --i) z[i] = p *= z[i];
+        } else if (tid == 1) {
+            double p = 1.0;
+            for (int i = at + 1; i < m; ++i) z[i] = p *= z[i];
+        }
+        __syncthreads();
+        double n2 = 0.0;
+        for (int i = lane; i < m; i += 64) n2 = fma(z[i], z[i], n2);
+        const double next = shift + gamma * eig::rcp_of(eig::sum64(n2));
+        if (pass == 1) {
+            if (tid == 0) g.e1[blockIdx.x] = next;
+        }
+        shift = next;
     }
-    __syncthreads();
-    a = 0.0;
-    b = 0.0;
-    for (int w = 0; w < nw; ++w) {
-        a += red[2 * w];
-        b += red[2 * w + 1];
+
+    // back to the grid: reflectors in reverse, by the first wavefront
+    if (tid >= 64) return;
+    constexpr int NL = MEM ? eig::kMax / 64 : (16 * CB + 63) / 64;
+    double y[NL], v[NL];
+#pragma unroll
+    for (int l = 0; l < NL; ++l) y[l] = lane + 64 * l < m ? z[lane + 64 * l] : 0.0;
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const int i = lane + 64 * l;
+            v[l] = s >= 0 && i > s && i < m ? refl[reflector_at(s, m) + i] : 0.0;
+        }
+    };
+    fetch(m - 2);
+    for (int s = m - 2; s >= 0; --s) {
+        double w[NL], dot = 0.0;
+        const double ts = tau[s];
+#pragma unroll
+        for (int l = 0; l < NL; ++l) w[l] = v[l];
+        fetch(s - 1);
+        if (ts != 0.0) {
+#pragma unroll
+            for (int l = 0; l < NL; ++l) dot = fma(w[l], y[l], dot);
+            dot = ts * eig::sum64(dot);
+#pragma unroll
+            for (int l = 0; l < NL; ++l) y[l] = fma(-dot, w[l], y[l]);
+        }
     }
-    __syncthreads();
+    double n2 = 0.0, big = 0.0;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+        n2 = fma(y[l], y[l], n2);
+        big = fmax(big, fabs(y[l]));
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+    double scale = 1.0 / sqrt(eig::sum64(n2));
+    // the first component of the largest magnitude is positive
+    bool found = false;
+#pragma unroll
+    for (int l = 0; l < NL; ++l) {
+        const unsigned long long b = __ballot(fabs(y[l]) == big);
+        if (!found && b != 0) {
+            found = true;
+            if (__shfl(y[l], __ffsll((long long)b) - 1, 64) < 0.0) scale = -scale;
+        }
+    }
+#pragma unroll
+    for (int l = 0; l < NL; ++l)
+        if (lane + 64 * l < m) g.phi[(size_t)blockIdx.x * m + lane + 64 * l] = scale * y[l];
 }
 
-__global__ void __launch_bounds__(kEdgeThreads) k_edge_jacobi(const double* circ, const double* vcol, const double* kx,
-                                                              int ny, double kappa, double inv_lb2, double y0,
-                                                              double dy, double* work, double* e1, double* phi) {
-    const int m = blockIdx.x;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const double k = kx[m];
-    double* A = work + (size_t)m * 2 * ny * ny;
-    double* V = A + (size_t)ny * ny;
-    __shared__ int sp[128], sq[128];
-    __shared__ double sc[128], ss[128];
-    __shared__ double red[2 * (kEdgeThreads / 64)];
-    __shared__ int s_min, s_sign;
-
-    for (int idx = tid; idx < ny * ny; idx += nt) {
-        const int i = idx / ny, j = idx % ny;
-        double a = circ[(i - j + ny) % ny];
-        if (i == j) {
-            const double u = k - (y0 + dy * i) * inv_lb2;
-            a += kappa * u * u + vcol[i];
+// rows: grid rows per block (x_i), each on ny threads; the amplitudes and phases of
+// a row's waves are staged in LDS once instead of formed by each of its ny threads
+// (128 x 96: 67 -> 10 us).
+constexpr int kWaves = 1024;  // rows nx staged waves at most
+__global__ void __launch_bounds__(kThreads) k_edge_sum(EdgeArgs g, int rows) {
+    __shared__ double s_gap[kThreads];
+    __shared__ int s_at[kThreads];
+    __shared__ double2 wave[kWaves];
+    __shared__ double red[kThreads / 64];
+    const int tid = threadIdx.x, nx = g.nx, ny = g.ny;
+    // first grid index on the requested side whose level is closest to the target
+    double gap = 1e300;
+    int at = nx;
+    for (int m = tid; m < nx; m += kThreads) {
+        const double k = g.kx[m];
+        const double d = fabs(g.e1[m] - g.target);
+        if ((g.top ? k > 0.0 : k < 0.0) && (at == nx || d < gap)) {
+            gap = d;
+            at = m;
         }
-        A[idx] = a;
-        V[idx] = (i == j) ? 1.0 : 0.0;
     }
+    s_gap[tid] = gap;
+    s_at[tid] = at;
     __syncthreads();
-
-    const int half = ny / 2;
-    double prev_off = -1.0;
-    for (int sweep = 0; sweep < kEdgeMaxSweeps; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int idx = tid; idx < ny * ny; idx += nt) {
-            const double a = A[idx];
-            tot += a * a;
-            if (idx / ny != idx % ny) off += a * a;
-        }
-        block_sum2(off, tot, red);
-        // converged, or stalled at rounding level: quadratic convergence would
-        // have shrunk it by far more than a factor 4, and a stall counts only once
-        // the off-diagonal part is already small (where the sweeps stall, rounding
-        // leaves 2e-33 to 7e-33 of the total at ny = 64 and 256), not during the
-        // slower first sweeps
-        if (off == 0.0 || off <= 1e-32 * tot ||
-            (sweep > 3 && prev_off >= 0.0 && off > 0.25 * prev_off && off <= 1e-24 * tot))
-            break;
-        prev_off = off;
-        for (int r = 0; r < ny - 1; ++r) {
-            if (tid < half) {
-                // round robin: index ny - 1 meets r, and (r + i, r - i) mod (ny - 1) meet
-                int p, q;
-                if (tid == 0) {
-                    p = r;
-                    q = ny - 1;
-                } else {
-                    p = (r + tid) % (ny - 1);
-                    q = (r - tid + (ny - 1)) % (ny - 1);
-                }
-                if (p > q) {
-                    const int t = p;
-                    p = q;
-                    q = t;
-                }
-                const double apq = A[p * ny + q];
-                double c = 1.0, s = 0.0;
-                if (apq != 0.0) {
-                    // tan of the angle that zeroes a_pq: the smaller root of t^2 + 2 theta t - 1 = 0
-                    const double theta = (A[q * ny + q] - A[p * ny + p]) / (2.0 * apq);
-                    const double at = fabs(theta);
-                    double t = (at > 1e150) ? 0.5 / at : 1.0 / (at + sqrt(at * at + 1.0));
-                    if (theta < 0.0) t = -t;
-                    c = 1.0 / sqrt(t * t + 1.0);
-                    s = t * c;
-                }
-                sp[tid] = p;
-                sq[tid] = q;
-                sc[tid] = c;
-                ss[tid] = s;
+    for (int o = kThreads / 2; o >= 1; o >>= 1) {
+        if (tid < o) {
+            const double og = s_gap[tid + o];
+            const int oa = s_at[tid + o];
+            if (oa < nx && (s_at[tid] == nx || og < s_gap[tid] || (og == s_gap[tid] && oa < s_at[tid]))) {
+                s_gap[tid] = og;
+                s_at[tid] = oa;
             }
-            __syncthreads();
-            for (int w = tid; w < half * ny; w += nt) {  // rows p, q of J^T A
-                const int i = w / ny, j = w % ny;
-                const int p = sp[i], q = sq[i];
-                const double c = sc[i], s = ss[i];
-                const double x = A[p * ny + j], y = A[q * ny + j];
-                A[p * ny + j] = c * x - s * y;
-                A[q * ny + j] = s * x + c * y;
-            }
-            __syncthreads();
-            for (int w = tid; w < half * ny; w += nt) {  // columns p, q of (J^T A) J and V J
-                const int i = w / ny, j = w % ny;
-                const int p = sp[i], q = sq[i];
-                const double c = sc[i], s = ss[i];
-                const double x = A[j * ny + p], y = A[j * ny + q];
-                A[j * ny + p] = c * x - s * y;
-                A[j * ny + q] = s * x + c * y;
-                const double vx = V[j * ny + p], vy = V[j * ny + q];
-                V[j * ny + p] = c * vx - s * vy;
-                V[j * ny + q] = s * vx + c * vy;
-            }
-            __syncthreads();
         }
+        __syncthreads();
     }
-
-    if (tid == 0) {
-        int b = 0;
-        for (int i = 1; i < ny; ++i)
-            if (A[i * ny + i] < A[b * ny + b]) b = i;
-        int jm = 0;
-        for (int j = 1; j < ny; ++j)
-            if (fabs(V[j * ny + b]) > fabs(V[jm * ny + b])) jm = j;
-        s_min = b;
-        s_sign = V[jm * ny + b] < 0.0 ? -1 : 1;
-        e1[m] = A[b * ny + b];
+    const int best = s_at[0] < nx ? s_at[0] : 0;  // every supported nx has wave numbers of both signs
+    const double k0 = g.kx[best];
+    if (blockIdx.x == 0 && tid == 0) {
+        g.info[0] = k0;
+        g.info[1] = g.e1[best];
+        g.info[2] = g.target;
     }
-    __syncthreads();
-    for (int j = tid; j < ny; j += nt) phi[(size_t)m * ny + j] = s_sign * V[j * ny + s_min];
-}
-
-// block i: the row x_i of the packet, thread j: y_j
-__global__ void k_edge_sum(const double* kx, const double* e1, const double* phi, int nx, int ny, int top,
-                           double target, double sigma, double xc, double x0, double dx, double2* psi,
-                           double* part, double* info) {
-    __shared__ int s_i0;
-    __shared__ double s_n2[256];
-    const int i = blockIdx.x, j = threadIdx.x;
-    if (j == 0) {
-        // first grid index on the requested side whose level is closest to the target
-        int best = -1;
-        for (int m = 0; m < nx; ++m) {
-            const bool side = top ? (kx[m] > 0.0) : (kx[m] < 0.0);
-            if (!side) continue;
-            if (best < 0 || fabs(e1[m] - target) < fabs(e1[best] - target)) best = m;
-        }
-        if (best < 0) best = 0;  // not reached: every supported nx has wave numbers of both signs
-        s_i0 = best;
-        if (i == 0) {
-            info[0] = kx[best];
-            info[1] = e1[best];
-            info[2] = target;
-        }
-    }
-    __syncthreads();
-    const double k0 = kx[s_i0];
-    const double x = x0 + dx * i;
-    double re = 0.0, im = 0.0;
-    for (int m = 0; m < nx; ++m) {
-        const double d = kx[m] - k0;
-        const double amp = exp(-sigma * sigma * d * d);
+    const int i0 = blockIdx.x * rows;
+    for (int q = tid; q < rows * nx; q += kThreads) {
+        const int m = q % nx;
+        const double k = g.kx[m], d = k - k0;
+        const double amp = exp(-g.sigma * g.sigma * d * d);
         double sn, cs;
-        sincos(kx[m] * (x - xc), &sn, &cs);
-        const double f = amp * phi[(size_t)m * ny + j];
-        re += f * cs;
-        im += f * sn;
+        sincos(k * (g.x0 + g.dx * (i0 + q / nx) - g.xc), &sn, &cs);
+        wave[q] = make_double2(amp * cs, amp * sn);
     }
-    psi[(size_t)i * ny + j] = make_double2(re, im);
-    s_n2[j] = re * re + im * im;
     __syncthreads();
-    if (j == 0) {  // the row's squared modulus, summed in y order
-        double t = 0.0;
-        for (int q = 0; q < ny; ++q) t += s_n2[q];
-        part[i] = t;
+    const int r = tid / ny, j = tid % ny, i = i0 + r;
+    double n2 = 0.0;
+    if (r < rows && i < nx) {
+        double re = 0.0, im = 0.0;
+#pragma unroll 8
+        for (int m = 0; m < nx; ++m) {
+            const double f = g.phi[(size_t)m * ny + j];
+            const double2 w = wave[r * nx + m];
+            re = fma(w.x, f, re);
+            im = fma(w.y, f, im);
+        }
+        g.psi[(size_t)i * ny + j] = make_double2(re, im);
+        n2 = re * re + im * im;
     }
+    const double s = block_sum(n2, red);
+    if (tid == 0) g.part[blockIdx.x] = s;
 }
 
-__global__ void k_edge_scale(double2* psi, const double* part, int nx, int ny) {
+__global__ void __launch_bounds__(kThreads) k_edge_scale(double2* psi, const double* part, int nparts, int count) {
+    __shared__ double red[kThreads / 64];
     __shared__ double s_inv;
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int i = 0; i < nx; ++i) t += part[i];
-        s_inv = 1.0 / sqrt(t);
-    }
+    const int tid = threadIdx.x;
+    double a = 0.0;
+    for (int q = tid; q < nparts; q += kThreads) a += part[q];
+    const double s = block_sum(a, red);
+    if (tid == 0) s_inv = 1.0 / sqrt(s);
     __syncthreads();
-    const size_t idx = (size_t)blockIdx.x * ny + threadIdx.x;
-    const double2 v = psi[idx];
-    psi[idx] = make_double2(v.x * s_inv, v.y * s_inv);
+    const int idx = blockIdx.x * kThreads + tid;
+    if (idx < count) psi[idx] = cscale(psi[idx], s_inv);
+}
+
+template <int RA, int CB, bool MEM>
+hipError_t launch_edge_state(const EdgeArgs& e, hipStream_t s) {
+    const size_t lds = MEM ? 0 : (size_t)e.ny * (e.ny - 1) / 2 * sizeof(double);
+    auto fn = k_edge_state<RA, CB, MEM>;
+    if (lds > 32 * 1024) {
+        // with its static LDS the block is past 64 KB, which has to be allowed
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+        if (err != hipSuccess) return err;
+    }
+    hipLaunchKernelGGL(fn, dim3(e.nx), dim3(kThreads), lds, s, e);
+    return hipGetLastError();
 }
 
 }  // namespace
 
+size_t edge_work_doubles(int nx, int ny) {
+    return ny > eig::kRegMax ? (size_t)nx * ((size_t)ny * ny + (size_t)ny * (ny - 1) / 2) : 0;
+}
+
 hipError_t launch_edge_packet(const EdgeArgs& e, hipStream_t s) {
-    // even ny (the round-robin pairs), at most 256 (one thread per y in the packet kernels)
-    if (e.nx <= 0 || e.ny < 4 || e.ny > 256 || (e.ny % 2) != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_edge_jacobi, dim3(e.nx), dim3(kEdgeThreads), 0, s, e.circ, e.vcol, e.kx, e.ny, e.kappa,
-                       e.inv_lb2, e.y0, e.dy, e.work, e.e1, e.phi);
-    hipError_t err = hipGetLastError();
+    if (e.nx <= 0 || e.nx > kWaves / 4 || e.ny < 4 || e.ny > eig::kMax) return hipErrorInvalidValue;
+    hipError_t err = e.ny <= 32    ? launch_edge_state<2, 2, false>(e, s)
+                     : e.ny <= 64  ? launch_edge_state<4, 4, false>(e, s)
+                     : e.ny <= 128 ? launch_edge_state<8, 8, false>(e, s)
+                                   : launch_edge_state<8, 8, true>(e, s);
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_edge_sum, dim3(e.nx), dim3(e.ny), 0, s, e.kx, e.e1, e.phi, e.nx, e.ny, e.top, e.target,
-                       e.sigma, e.xc, e.x0, e.dx, e.psi, e.part, e.info);
+    int rows = kThreads / e.ny;
+    if (rows > kWaves / e.nx) rows = kWaves / e.nx;
+    const int nblocks = (e.nx + rows - 1) / rows, count = e.nx * e.ny;
+    hipLaunchKernelGGL(k_edge_sum, dim3(nblocks), dim3(kThreads), 0, s, e, rows);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_edge_scale, dim3(e.nx), dim3(e.ny), 0, s, e.psi, e.part, e.nx, e.ny);
+    hipLaunchKernelGGL(k_edge_scale, dim3((count + kThreads - 1) / kThreads), dim3(kThreads), 0, s, e.psi, e.part,
+                       nblocks, count);
     return hipGetLastError();
 }
 

@@ -1260,20 +1260,23 @@ int hom4d_edge_packet(hom4d* h, const double* v_col, double sigma_x_nm, double x
     for (int j = 0; j < ny; ++j)
         if (!std::isfinite(v_col[j])) return fail(HOM4D_EINVAL, "v_col[%d] is not finite", j);
     // first row of the spectral kinetic matrix kappa (-d^2/dy^2) on the periodic y grid
-    std::vector<double> host((size_t)2 * ny + nx);
+    std::vector<double> host((size_t)2 * ny + nx), cosine(ny), k2(ny);
+    for (int m = 0; m < ny; ++m) {
+        const double k = kgrid(ny, c.ly_nm, m);
+        k2[m] = k * k;
+        cosine[m] = std::cos(2.0 * M_PI * (double)m / ny);
+    }
     double* circ = host.data();
     for (int d = 0; d < ny; ++d) {
         double acc = 0.0;
-        for (int m = 0; m < ny; ++m) {
-            const double k = kgrid(ny, c.ly_nm, m);
-            acc += k * k * std::cos(2.0 * M_PI * (double)((m * d) % ny) / ny);
-        }
+        for (int m = 0; m < ny; ++m) acc += k2[m] * cosine[(m * d) % ny];
         circ[d] = h->u.kappa * acc / ny;
     }
     std::memcpy(host.data() + ny, v_col, ny * sizeof(double));
     for (int m = 0; m < nx; ++m) host[2 * ny + m] = kgrid(nx, c.lx_nm, m);
-    // device: circ, v, kx | work 2 nx ny^2 | e1 nx | phi nx ny | psi 2 nx ny | part nx | info 3
-    const size_t n_in = host.size(), n_work = (size_t)2 * nx * ny * ny;
+    // device: circ, v, kx | work | e1 nx | phi nx ny | psi 2 nx ny | part nx | info 3
+    // (psi on a 16-byte boundary: everything before it is an even number of doubles)
+    const size_t n_in = host.size(), n_work = edge_work_doubles(nx, ny);
     const size_t total = n_in + n_work + nx + (size_t)nx * ny + (size_t)2 * nx * ny + nx + 3;
     double* dev = nullptr;
     HIP_TRY(hipMalloc((void**)&dev, total * sizeof(double)));

@@ -175,8 +175,9 @@ hipError_t launch_zero(double* p, int64_t count, hipStream_t s);
 
 // Edge states of every grid wave number along x and one Gaussian edge-state
 // packet built from them (edge_states.hip).  Device pointers: circ [ny] (first
-// row of the spectral kinetic matrix), vcol [ny], kx [nx], work [2 nx ny^2],
-// e1 [nx], phi [nx ny], psi [nx ny], part [nx], info [3] = (k0, E(k0), target).
+// row of the spectral kinetic matrix), vcol [ny], kx [nx], work
+// [edge_work_doubles(nx, ny)], e1 [nx], phi [nx ny], psi [nx ny], part [nx],
+// info [3] = (k0, E(k0), target).
 struct EdgeArgs {
     const double* circ;
     const double* vcol;
@@ -192,6 +193,7 @@ struct EdgeArgs {
     double* part;
     double* info;
 };
+size_t edge_work_doubles(int nx, int ny);
 hipError_t launch_edge_packet(const EdgeArgs& e, hipStream_t s);
 
 // Fixed device scratch of the no-allocation reverse sweep: kScratchDoubles
