@@ -222,7 +222,7 @@ int hom4d_conditional(hom4d* h, int32_t ix2, int32_t jy2, double* out);
  * eigenpair of the transverse Hamiltonian
  *     H(k) = kappa [ -d^2/dy^2 + (k - y eB/hbar)^2 ] + v_col(y)
  * (gauge A = (-B y, 0), second derivative spectral on the periodic y grid) is
- * found on the GPU (Jacobi, FP64), its sign fixed so that the largest-magnitude
+ * found on the GPU (FP64), its sign fixed so that the largest-magnitude
  * component is positive; k0 is the wave number, among k > 0 (top = 1) or k < 0
  * (top = 0), whose level is closest to hbar omega_c / 2 + e_above_lll_mev; and
  *     psi(x, y) = sum_k exp(-sigma_x^2 (k - k0)^2) exp(i k (x - xc)) phi_k(y),

@@ -220,9 +220,7 @@ struct hom4d {
     double* v_dev = nullptr;     // [nx*ny] meV
     double* w_dev = nullptr;     // [nx*ny] region weights
     double* red_part = nullptr;  // reduction partials
-    double* red_out = nullptr;   // 8 doubles
-    double* host_out = nullptr;  // pinned, 8 doubles
-    int red_blocks = 0;
+    double* host_out = nullptr;  // pinned, 8 doubles, written by the last reduction kernel
     // slices
     int32_t* ix_dev = nullptr;   // 512 ints
     double2* slice_dev = nullptr;// 256*256 slice values, 256*256 density matrix, kSliceScratch doubles
@@ -558,9 +556,9 @@ int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradC
 
 
 
-int fetch_reduction(hom4d* h, int width, double* out) {
-    HIP_TRY(launch_reduce_parts(h->red_part, h->red_blocks, width, h->red_out, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->host_out, h->red_out, width * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+// Sums of nparts partial sums of the given width; they go straight to pinned host memory.
+int fetch_reduction(hom4d* h, int nparts, int width, double* out) {
+    HIP_TRY(launch_reduce_parts(h->red_part, nparts, width, nullptr, h->host_out, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     for (int q = 0; q < width; ++q) out[q] = h->host_out[q];
     return HOM4D_OK;
@@ -658,9 +656,10 @@ constexpr char kCkptMagic[8] = {'H', 'O', 'M', '4', 'D', 'C', 'K', '1'};
 // FP64 norm of the bound state (one reduction pass).
 int state_norm(hom4d* h, double* out) {
     HIP_TRY(hipMemsetAsync(h->w_dev, 0, h->nxy * sizeof(double), h->stream));
-    HIP_TRY(launch_obs(h->psi, h->mixed, h->w_dev, h->nxy, h->red_part, h->red_blocks, h->stream));
+    int nparts = 0;
+    HIP_TRY(launch_obs(h->psi, h->mixed, h->w_dev, h->nxy, h->red_part, &nparts, h->stream));
     double r[5];
-    int rc = fetch_reduction(h, 5, r);
+    int rc = fetch_reduction(h, nparts, 5, r);
     if (rc) return rc;
     *out = r[0];
     return HOM4D_OK;
@@ -668,7 +667,7 @@ int state_norm(hom4d* h, double* out) {
 
 void free_all(hom4d* h) {
     void* bufs[] = {h->tw_x, h->tw_y, h->kx_half, h->kx_full, h->kxt_half, h->kxt_full, h->ky_full, h->a1_half, h->ac_half, h->v_dev,
-                    h->w_dev, h->red_part, h->red_out, h->ix_dev, h->slice_dev, h->orb_dev, h->g_buf};
+                    h->w_dev, h->red_part, h->ix_dev, h->slice_dev, h->orb_dev, h->g_buf};
     for (void* b : bufs)
         if (b) (void)hipFree(b);
     if (h->host_out) (void)hipHostFree(h->host_out);
@@ -734,10 +733,10 @@ int grad_sweep(hom4d* h, const double* w_top, const double* coeffs, void* d_lamb
     int rc;
     HIP_TRY(launch_zero(buf, (int64_t)l.total, h->stream));
     HIP_TRY(hipMemcpyAsync(h->w_dev, w_top, h->nxy * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(launch_loss_lambda(h->psi, d_lambda, h->mixed, h->w_dev, coeffs, h->nxy, h->red_part, h->red_blocks,
-                               h->stream));
+    int nparts = 0;
+    HIP_TRY(launch_loss_lambda(h->psi, d_lambda, h->mixed, h->w_dev, coeffs, h->nxy, h->red_part, &nparts, h->stream));
     double L = 0.0;
-    if ((rc = fetch_reduction(h, 1, &L))) return rc;
+    if ((rc = fetch_reduction(h, nparts, 1, &L))) return rc;
     // reverse sweep, segment by segment, restoring the state at every checkpoint
     int64_t seg_end = h->rec_steps;
     for (int64_t k = h->rec_steps / h->ckpt_every; k >= 0; --k) {
@@ -753,8 +752,7 @@ int grad_sweep(hom4d* h, const double* w_top, const double* coeffs, void* d_lamb
                                c.ny, c.dt_fs / h->u.hbar, dldv_dev, h->stream));
     HIP_TRY(hipMemcpyAsync(dL_dV, dldv_dev, h->nxy * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     // dL/dB: both x axes, Parseval factor 1/nx, factor 2 of 2 Im(conj(lambda) psi)
-    HIP_TRY(launch_reduce_parts(g.gb_x1, (int)(l.nb_x1 + l.nb_x2), 1, h->red_out, h->stream));
-    HIP_TRY(hipMemcpyAsync(h->host_out, h->red_out, sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(launch_reduce_parts(g.gb_x1, (int)(l.nb_x1 + l.nb_x2), 1, h->red_part, h->host_out, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     *dL_dB = h->host_out[0] * 2.0 / c.nx;
     *loss = L;
@@ -789,7 +787,6 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
     h->nxy = cfg->nx * cfg->ny;
     h->npts = (int64_t)h->nxy * h->nxy;
     h->state_bytes = hom4d_state_bytes(cfg);
-    h->red_blocks = std::min(h->nxy, 1024);
     auto cleanup = [&](int code) {
         free_all(h);
         delete h;
@@ -816,8 +813,7 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
         {(void**)&h->ac_half, (size_t)(2 * nx - 1) * (2 * ny - 1) * sizeof(double2)},
         {(void**)&h->v_dev, (size_t)nx * ny * sizeof(double)},
         {(void**)&h->w_dev, (size_t)nx * ny * sizeof(double)},
-        {(void**)&h->red_part, (size_t)h->red_blocks * 8 * sizeof(double)},
-        {(void**)&h->red_out, 8 * sizeof(double)},
+        {(void**)&h->red_part, (size_t)std::max(5 * reduction_parts(h->nxy, h->mixed), kReduceBlocks) * sizeof(double)},
         {(void**)&h->ix_dev, 512 * sizeof(int32_t)},
         {(void**)&h->slice_dev, 2 * 256 * 256 * sizeof(double2) + kSliceScratch * sizeof(double)},
         {(void**)&h->orb_dev, (size_t)2 * nx * ny * sizeof(double2)},
@@ -908,9 +904,10 @@ int hom4d_init_state(hom4d* h, const double* psi_a, const double* psi_b, int32_t
     const size_t nb = (size_t)h->nxy * sizeof(double2);
     HIP_TRY(hipMemcpyAsync(h->orb_dev, psi_a, nb, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->orb_dev + h->nxy, psi_b, nb, hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(launch_init_norm(h->orb_dev, h->orb_dev + h->nxy, sym, h->nxy, h->red_part, h->red_blocks, h->stream));
+    int nparts = 0;
+    HIP_TRY(launch_init_norm(h->orb_dev, h->orb_dev + h->nxy, sym, h->nxy, h->red_part, &nparts, h->stream));
     double nrm = 0.0;
-    int rc = fetch_reduction(h, 1, &nrm);
+    int rc = fetch_reduction(h, nparts, 1, &nrm);
     if (rc) return rc;
     if (!(nrm > 0.0) || !std::isfinite(nrm)) return fail(HOM4D_EINVAL, "initial state has norm %g", nrm);
     HIP_TRY(launch_init_write(h->psi, h->mixed, h->orb_dev, h->orb_dev + h->nxy, sym, h->nxy, 1.0 / std::sqrt(nrm),
@@ -1084,9 +1081,10 @@ int hom4d_observables(hom4d* h, const double* w_top, hom4d_obs* out) {
     if (rc) return rc;
     if (!h->psi) return fail(HOM4D_EUNBOUND, "no state bound");
     HIP_TRY(hipMemcpyAsync(h->w_dev, w_top, h->nxy * sizeof(double), hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(launch_obs(h->psi, h->mixed, h->w_dev, h->nxy, h->red_part, h->red_blocks, h->stream));
+    int nparts = 0;
+    HIP_TRY(launch_obs(h->psi, h->mixed, h->w_dev, h->nxy, h->red_part, &nparts, h->stream));
     double r[5];
-    if ((rc = fetch_reduction(h, 5, r))) return rc;
+    if ((rc = fetch_reduction(h, nparts, 5, r))) return rc;
     out->norm = r[0];
     out->p_tt = r[1];
     out->p_tb = r[2];
@@ -1105,8 +1103,7 @@ int hom4d_marginal(hom4d* h, double* out) {
     if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
     if (!out) return fail(HOM4D_EINVAL, "out is NULL");
     if (!h->psi) return fail(HOM4D_EUNBOUND, "no state bound");
-    // the reduction partial buffer has room for red_blocks * 8 >= nx*ny doubles only if
-    // nx*ny <= 8 * red_blocks; the slice buffer (256*256 complex) always does
+    // the slice buffer (256*256 complex) has room for any nx*ny doubles
     double* dst = reinterpret_cast<double*>(h->slice_dev);
     HIP_TRY(launch_marginal(h->psi, h->mixed, h->nxy, dst, h->stream));
     HIP_TRY(hipMemcpyAsync(out, dst, h->nxy * sizeof(double), hipMemcpyDeviceToHost, h->stream));

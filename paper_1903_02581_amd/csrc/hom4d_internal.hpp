@@ -139,17 +139,23 @@ hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const Pa
 bool plane_available(int nx, int ny, bool mixed);
 hipError_t launch_plane(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s);
 
-// Reductions and elementwise kernels.
-hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part,
-                            int nblocks, hipStream_t s);
+// Reductions and elementwise kernels over all pairs (r1, r2).  The reductions say
+// in *nparts how many partial sums (of their width) they write; at most
+// reduction_parts(nxy, mixed).
+int reduction_parts(int nxy, bool mixed);
+hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part, int* nparts,
+                            hipStream_t s);
 hipError_t launch_init_write(void* psi, bool mixed, const double2* pa, const double2* pb, int sym,
                              int nxy, double scale, hipStream_t s);
-hipError_t launch_obs(const void* psi, bool mixed, const double* w, int nxy, double* part, int nblocks,
+hipError_t launch_obs(const void* psi, bool mixed, const double* w, int nxy, double* part, int* nparts,
                       hipStream_t s);
-hipError_t launch_loss_lambda(const void* psi, void* lam, bool mixed, const double* w,
-                              const double* coeffs_dev, int nxy, double* part, int nblocks,
-                              hipStream_t s);
-hipError_t launch_reduce_parts(const double* part, int nparts, int width, double* out, hipStream_t s);
+hipError_t launch_loss_lambda(const void* psi, void* lam, bool mixed, const double* w, const double* coeffs,
+                              int nxy, double* part, int* nparts, hipStream_t s);
+// out[q] = sum over the nparts partial sums of width values; scratch:
+// kReduceBlocks doubles (used where width = 1).
+constexpr int kReduceBlocks = 256;
+hipError_t launch_reduce_parts(const double* part, int nparts, int width, double* scratch, double* out,
+                               hipStream_t s);
 hipError_t launch_gather(const void* psi, bool mixed, const int32_t* ix1, int n1, int jy1,
                          const int32_t* ix2, int n2, int jy2, int nx, int ny, double2* out,
                          hipStream_t s);
@@ -166,8 +172,6 @@ hipError_t launch_slice_entropy(const void* psi, bool mixed, const SliceIndex& i
                                 hipStream_t s);
 hipError_t launch_marginal(const void* psi, bool mixed, int nxy, double* out, hipStream_t s);
 hipError_t launch_conditional(const void* psi, bool mixed, int nxy, int r2, double* out, hipStream_t s);
-hipError_t launch_c128_to_c64(const double2* in, float2* out, int64_t count, hipStream_t s);
-hipError_t launch_c64_to_c128(const float2* in, double2* out, int64_t count, hipStream_t s);
 hipError_t launch_grad_finish(const double* m_x2, int bpr_x2, const double* m_y2, int bpr_y2,
                               const double* m_y1, const double* m_x1, int nx, int ny, double gscale,
                               double* dldv, hipStream_t s);

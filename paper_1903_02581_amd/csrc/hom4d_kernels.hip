@@ -48,64 +48,162 @@ namespace {
 using namespace dev;
 
 // --------------------------------------------------------------------------------------
-// Elementwise / reduction kernels.  Rows r1 are spread over blocks, r2 over threads, so
-// the summation order depends only on the launch shape: results are bitwise repeatable.
+// Elementwise / reduction kernels over all pairs (r1, r2).  A block takes one chunk of
+// r2 and a strided set of rows r1: every thread keeps its r2 table entries
+// (weights, orbitals) in registers over its rows and moves 16 bytes of state per
+// load or store, K of them per row, where one pair per thread and load re-read the
+// tables for every point and kept one 8- or 16-byte access in flight.  Bound by HBM
+// (init_norm by its FP64 products): 128x96 complex128 init_write 576 -> 438 us (5.5
+// TB/s), init_norm 230 -> 111; 256x128 complex64 2.67 -> 1.57 ms and 1.55 -> 0.77;
+// 128x64 complex64 obs 164 -> 131 us, loss_lambda 246 -> 182.  The summation order
+// depends only on the launch shape: results are bitwise repeatable.
 
-__global__ void k_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part) {
-    __shared__ double red[256];
+constexpr int kPairThreads = 256;
+constexpr int kPairBlocks = 2048;  // eight 256-thread blocks per CU
+template <class S>
+constexpr int kVec = 16 / (int)sizeof(S);  // state elements per access
+
+template <class S>
+__device__ __forceinline__ void ld16(const S* p, double2* v) {
+    if constexpr (std::is_same<S, double2>::value) {
+        v[0] = *p;
+    } else {
+        const float4 f = *reinterpret_cast<const float4*>(p);
+        v[0] = make_double2((double)f.x, (double)f.y);
+        v[1] = make_double2((double)f.z, (double)f.w);
+    }
+}
+template <class S>
+__device__ __forceinline__ void st16(S* p, const double2* v) {
+    if constexpr (std::is_same<S, double2>::value)
+        *p = v[0];
+    else
+        *reinterpret_cast<float4*>(p) = make_float4((float)v[0].x, (float)v[0].y, (float)v[1].x, (float)v[1].y);
+}
+
+// The r2 positions of a thread: K groups of kVec<S> consecutive ones (nxy is a
+// multiple of 16, so a group is inside the row or outside it).
+template <class S, int K>
+struct PairTile {
+    int pos[K];
+    bool in[K];
+    __device__ __forceinline__ explicit PairTile(int nxy) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            pos[k] = (((int)blockIdx.x * K + k) * kPairThreads + (int)threadIdx.x) * kVec<S>;
+            in[k] = pos[k] < nxy;
+        }
+    }
+};
+
+// psi_a(r1) psi_b(r2) + sym psi_b(r1) psi_a(r2)
+__device__ __forceinline__ double2 pair_value(double2 a1, double2 b1, double2 a2, double2 b2, int sym) {
+    double2 p = cmul(a1, b2);
+    if (sym != 0) {
+        const double2 q = cmul(b1, a2);
+        p = make_double2(p.x + sym * q.x, p.y + sym * q.y);
+    }
+    return p;
+}
+
+template <int K>
+__global__ void __launch_bounds__(kPairThreads) k_init_norm(const double2* pa, const double2* pb, int sym, int nxy,
+                                                            double* part) {
+    __shared__ double red[kPairThreads / 64];
+    const PairTile<double2, K> tile(nxy);
+    double2 a2[K], b2[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) a2[k] = b2[k] = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (tile.in[k]) {
+            a2[k] = pa[tile.pos[k]];
+            b2[k] = pb[tile.pos[k]];
+        }
     double acc = 0.0;
-    for (int r1 = blockIdx.x; r1 < nxy; r1 += gridDim.x) {
+    for (int r1 = blockIdx.y; r1 < nxy; r1 += gridDim.y) {
         const double2 a1 = pa[r1], b1 = pb[r1];
-        for (int r2 = threadIdx.x; r2 < nxy; r2 += blockDim.x) {
-            double2 p = cmul(a1, pb[r2]);
-            if (sym != 0) {
-                const double2 q = cmul(b1, pa[r2]);
-                p = make_double2(p.x + sym * q.x, p.y + sym * q.y);
-            }
-            acc += p.x * p.x + p.y * p.y;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const double2 p = pair_value(a1, b1, a2[k], b2[k], sym);
+            if (tile.in[k]) acc += p.x * p.x + p.y * p.y;
         }
     }
     const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = s;
+    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
-template <class S>
-__global__ void k_init_write(S* psi, const double2* pa, const double2* pb, int sym, int nxy, double scale) {
-    for (int r1 = blockIdx.x; r1 < nxy; r1 += gridDim.x) {
-        const double2 a1 = pa[r1], b1 = pb[r1];
-        for (int r2 = threadIdx.x; r2 < nxy; r2 += blockDim.x) {
-            double2 p = cmul(a1, pb[r2]);
-            if (sym != 0) {
-                const double2 q = cmul(b1, pa[r2]);
-                p = make_double2(p.x + sym * q.x, p.y + sym * q.y);
+template <class S, int K>
+__global__ void __launch_bounds__(kPairThreads) k_init_write(S* psi, const double2* pa, const double2* pb, int sym,
+                                                             int nxy, double scale) {
+    constexpr int V = kVec<S>;
+    const PairTile<S, K> tile(nxy);
+    double2 a2[K][V], b2[K][V];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int q = 0; q < V; ++q) {
+            a2[k][q] = b2[k][q] = make_double2(0.0, 0.0);
+            if (tile.in[k]) {
+                a2[k][q] = pa[tile.pos[k] + q];
+                b2[k][q] = pb[tile.pos[k] + q];
             }
-            st<S>(psi + (int64_t)r1 * nxy + r2, cscale(p, scale));
+        }
+    for (int r1 = blockIdx.y; r1 < nxy; r1 += gridDim.y) {
+        const double2 a1 = pa[r1], b1 = pb[r1];
+        S* row = psi + (int64_t)r1 * nxy;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            double2 v[V];
+#pragma unroll
+            for (int q = 0; q < V; ++q) v[q] = cscale(pair_value(a1, b1, a2[k][q], b2[k][q], sym), scale);
+            if (tile.in[k]) st16<S>(row + tile.pos[k], v);
         }
     }
 }
 
-template <class S>
-__global__ void k_obs(const S* psi, const double* w, int nxy, double* part) {
-    __shared__ double red[256];
+template <class S, int K>
+__global__ void __launch_bounds__(kPairThreads) k_obs(const S* psi, const double* w, int nxy, double* part) {
+    constexpr int V = kVec<S>;
+    __shared__ double red[kPairThreads / 64];
+    const PairTile<S, K> tile(nxy);
+    double w2[K][V];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int q = 0; q < V; ++q) w2[k][q] = tile.in[k] ? w[tile.pos[k] + q] : 0.0;
     double acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int r1 = blockIdx.x; r1 < nxy; r1 += gridDim.x) {
-        const double w1 = w[r1];
+    for (int r1 = blockIdx.y; r1 < nxy; r1 += gridDim.y) {
         const S* row = psi + (int64_t)r1 * nxy;
-        for (int r2 = threadIdx.x; r2 < nxy; r2 += blockDim.x) {
-            const double2 p = ld<S>(row + r2);
-            const double d = p.x * p.x + p.y * p.y;
-            const double w2 = w[r2];
-            acc[0] += d;
-            acc[1] += w1 * w2 * d;
-            acc[2] += w1 * (1.0 - w2) * d;
-            acc[3] += (1.0 - w1) * w2 * d;
-            acc[4] += (1.0 - w1) * (1.0 - w2) * d;
+        double2 p[K][V];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int q = 0; q < V; ++q) p[k][q] = make_double2(0.0, 0.0);
+            if (tile.in[k]) ld16<S>(row + tile.pos[k], p[k]);
         }
+        // the row's sums over this thread's r2: all, top and bottom weighted
+        double all = 0.0, top = 0.0, bottom = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+                const double d = p[k][q].x * p[k][q].x + p[k][q].y * p[k][q].y;
+                all += d;
+                top += w2[k][q] * d;
+                bottom += (1.0 - w2[k][q]) * d;
+            }
+        const double w1 = w[r1];
+        acc[0] += all;
+        acc[1] += w1 * top;
+        acc[2] += w1 * bottom;
+        acc[3] += (1.0 - w1) * top;
+        acc[4] += (1.0 - w1) * bottom;
     }
 #pragma unroll
     for (int q = 0; q < 5; ++q) {
         const double s = block_sum(acc[q], red);
-        if (threadIdx.x == 0) part[blockIdx.x * 5 + q] = s;
+        if (threadIdx.x == 0) part[(blockIdx.y * gridDim.x + blockIdx.x) * 5 + q] = s;
     }
 }
 
@@ -113,34 +211,54 @@ struct LossCoeffs {
     double c[4];
 };
 
-template <class S>
-__global__ void k_loss_lambda(const S* psi, S* lam, const double* w, LossCoeffs cf, int nxy, double* part) {
-    __shared__ double red[256];
+template <class S, int K>
+__global__ void __launch_bounds__(kPairThreads) k_loss_lambda(const S* psi, S* lam, const double* w, LossCoeffs cf,
+                                                              int nxy, double* part) {
+    constexpr int V = kVec<S>;
+    __shared__ double red[kPairThreads / 64];
+    const PairTile<S, K> tile(nxy);
+    double w2[K][V];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int q = 0; q < V; ++q) w2[k][q] = tile.in[k] ? w[tile.pos[k] + q] : 0.0;
     double acc = 0.0;
-    for (int r1 = blockIdx.x; r1 < nxy; r1 += gridDim.x) {
-        const double w1 = w[r1];
+    for (int r1 = blockIdx.y; r1 < nxy; r1 += gridDim.y) {
         const int64_t o = (int64_t)r1 * nxy;
-        for (int r2 = threadIdx.x; r2 < nxy; r2 += blockDim.x) {
-            const double2 p = ld<S>(psi + o + r2);
-            const double w2 = w[r2];
-            const double wl = cf.c[0] * w1 * w2 + cf.c[1] * w1 * (1.0 - w2) + cf.c[2] * (1.0 - w1) * w2 +
-                              cf.c[3] * (1.0 - w1) * (1.0 - w2);
-            acc += wl * (p.x * p.x + p.y * p.y);
-            st<S>(lam + o + r2, cscale(p, wl));
+        double2 p[K][V];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+#pragma unroll
+            for (int q = 0; q < V; ++q) p[k][q] = make_double2(0.0, 0.0);
+            if (tile.in[k]) ld16<S>(psi + o + tile.pos[k], p[k]);
+        }
+        const double w1 = w[r1];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            double2 v[V];
+#pragma unroll
+            for (int q = 0; q < V; ++q) {
+                const double wl = cf.c[0] * w1 * w2[k][q] + cf.c[1] * w1 * (1.0 - w2[k][q]) +
+                                  cf.c[2] * (1.0 - w1) * w2[k][q] + cf.c[3] * (1.0 - w1) * (1.0 - w2[k][q]);
+                acc += wl * (p[k][q].x * p[k][q].x + p[k][q].y * p[k][q].y);
+                v[q] = cscale(p[k][q], wl);
+            }
+            if (tile.in[k]) st16<S>(lam + o + tile.pos[k], v);
         }
     }
     const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) part[blockIdx.x] = s;
+    if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
-// out[q] = sum_b part[b * width + q], fixed order; one block per q.
-__global__ void k_reduce_parts(const double* part, int nparts, int width, double* out) {
-    __shared__ double red[256];
+// out[block * width + q] = sum of part[b * width + q] over the block's share of the
+// partial sums, fixed order; grid (width, blocks).
+__global__ void __launch_bounds__(256) k_reduce_parts(const double* part, int nparts, int width, double* out) {
+    __shared__ double red[4];
     const int q = blockIdx.x;
     double acc = 0.0;
-    for (int b = threadIdx.x; b < nparts; b += blockDim.x) acc += part[(int64_t)b * width + q];
+    for (int b = blockIdx.y * 256 + threadIdx.x; b < nparts; b += gridDim.y * 256) acc += part[(int64_t)b * width + q];
     const double s = block_sum(acc, red);
-    if (threadIdx.x == 0) out[q] = s;
+    if (threadIdx.x == 0) out[blockIdx.y * width + q] = s;
 }
 
 template <class S>
@@ -178,35 +296,47 @@ __global__ void k_conditional(const S* psi, int nxy, int r2, double* out) {
     out[r1] = p.x * p.x + p.y * p.y;
 }
 
-__global__ void k_c128_to_c64(const double2* in, float2* out, int64_t count) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = make_float2((float)in[i].x, (float)in[i].y);
-}
-
-__global__ void k_c64_to_c128(const float2* in, double2* out, int64_t count) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = make_double2((double)in[i].x, (double)in[i].y);
-}
-
 __global__ void k_zero(double* p, int64_t count) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
         p[i] = 0.0;
 }
 
-__global__ void k_grad_finish(const double* m_x2, int bpr_x2, const double* m_y2, int bpr_y2, const double* m_y1,
-                              const double* m_x1, int nx, int ny, double gscale, double* dldv) {
-    const int nxy = nx * ny;
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nxy) return;
-    double g1 = 0.0, g2 = 0.0;
-    for (int q = 0; q < bpr_x2; ++q) g1 += m_x2[(int64_t)r * bpr_x2 + q];
-    for (int q = 0; q < bpr_y2; ++q) g1 += m_y2[(int64_t)r * bpr_y2 + q];
-    for (int i = 0; i < nx; ++i) g2 += m_y1[(int64_t)i * nxy + r];
-    for (int j = 0; j < ny; ++j) g2 += m_x1[(int64_t)j * nxy + r];
-    dldv[r] = gscale * (g1 + g2);
+// dL/dV from the marginals: 16 table entries per 256-thread block, 16 threads sharing
+// the terms of each (one thread per entry summed up to nx + ny terms in a serial
+// chain of loads on a few blocks: 128x64 82 -> 10 us).  g1 then g2, each in thread order.
+constexpr int kFinishEntries = 16;
+__global__ void __launch_bounds__(256) k_grad_finish(const double* m_x2, int bpr_x2, const double* m_y2, int bpr_y2,
+                                                     const double* m_y1, const double* m_x1, int nx, int ny,
+                                                     double gscale, double* dldv) {
+    __shared__ double sum[16][kFinishEntries + 1];
+    const int nxy = nx * ny;  // a multiple of 16
+    const int c = threadIdx.x % kFinishEntries, t = threadIdx.x / kFinishEntries;
+    const int r = blockIdx.x * kFinishEntries + c;
+    double g = 0.0;
+    for (int q = t; q < bpr_x2; q += 16) g += m_x2[(int64_t)r * bpr_x2 + q];
+    for (int q = t; q < bpr_y2; q += 16) g += m_y2[(int64_t)r * bpr_y2 + q];
+    for (int i = t; i < nx; i += 16) g += m_y1[(int64_t)i * nxy + r];
+    for (int j = t; j < ny; j += 16) g += m_x1[(int64_t)j * nxy + r];
+    sum[t][c] = g;
+    __syncthreads();
+    if (t == 0) {
+        double a = 0.0;
+        for (int q = 0; q < 16; ++q) a += sum[q][c];
+        dldv[r] = gscale * a;
+    }
 }
 
-inline int obs_threads() { return 256; }
+// Grid of a pair kernel: K accesses per thread and row where a row fills them, chunks
+// of r2 by groups of rows, about kPairBlocks blocks (fixed by the sizes alone).
+template <class S>
+bool pair_k4(int nxy) { return nxy >= 4 * kPairThreads * kVec<S>; }
+template <class S>
+dim3 pair_grid(int nxy) {
+    const int span = (pair_k4<S>(nxy) ? 4 : 1) * kPairThreads * kVec<S>;
+    const int chunks = (nxy + span - 1) / span;
+    return dim3(chunks, std::min(nxy, std::max(1, kPairBlocks / chunks)));
+}
+inline int blocks_of(dim3 g) { return (int)(g.x * g.y); }
 
 }  // namespace
 
@@ -329,45 +459,73 @@ hipError_t launch_plane(int nx, int ny, bool mixed, const PassArgs& a, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part, int nblocks,
+int reduction_parts(int nxy, bool mixed) {
+    return std::max(blocks_of(pair_grid<double2>(nxy)), mixed ? blocks_of(pair_grid<float2>(nxy)) : 0);
+}
+
+hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part, int* nparts,
                             hipStream_t s) {
-    hipLaunchKernelGGL(k_init_norm, dim3(nblocks), dim3(obs_threads()), 0, s, pa, pb, sym, nxy, part);
+    const dim3 g = pair_grid<double2>(nxy);
+    *nparts = blocks_of(g);
+    auto fn = pair_k4<double2>(nxy) ? k_init_norm<4> : k_init_norm<1>;
+    hipLaunchKernelGGL(fn, g, dim3(kPairThreads), 0, s, pa, pb, sym, nxy, part);
     return hipGetLastError();
 }
 
+template <class S>
+static void init_write(S* psi, const double2* pa, const double2* pb, int sym, int nxy, double scale, hipStream_t s) {
+    auto fn = pair_k4<S>(nxy) ? k_init_write<S, 4> : k_init_write<S, 1>;
+    hipLaunchKernelGGL(fn, pair_grid<S>(nxy), dim3(kPairThreads), 0, s, psi, pa, pb, sym, nxy, scale);
+}
 hipError_t launch_init_write(void* psi, bool mixed, const double2* pa, const double2* pb, int sym, int nxy,
                              double scale, hipStream_t s) {
-    const int nb = nxy < 2048 ? nxy : 2048;
     if (mixed)
-        hipLaunchKernelGGL(k_init_write<float2>, dim3(nb), dim3(256), 0, s, (float2*)psi, pa, pb, sym, nxy, scale);
+        init_write((float2*)psi, pa, pb, sym, nxy, scale, s);
     else
-        hipLaunchKernelGGL(k_init_write<double2>, dim3(nb), dim3(256), 0, s, (double2*)psi, pa, pb, sym, nxy, scale);
+        init_write((double2*)psi, pa, pb, sym, nxy, scale, s);
     return hipGetLastError();
 }
 
-hipError_t launch_obs(const void* psi, bool mixed, const double* w, int nxy, double* part, int nblocks,
+template <class S>
+static int obs(const S* psi, const double* w, int nxy, double* part, hipStream_t s) {
+    const dim3 g = pair_grid<S>(nxy);
+    auto fn = pair_k4<S>(nxy) ? k_obs<S, 4> : k_obs<S, 1>;
+    hipLaunchKernelGGL(fn, g, dim3(kPairThreads), 0, s, psi, w, nxy, part);
+    return blocks_of(g);
+}
+hipError_t launch_obs(const void* psi, bool mixed, const double* w, int nxy, double* part, int* nparts,
                       hipStream_t s) {
-    if (mixed)
-        hipLaunchKernelGGL(k_obs<float2>, dim3(nblocks), dim3(obs_threads()), 0, s, (const float2*)psi, w, nxy, part);
-    else
-        hipLaunchKernelGGL(k_obs<double2>, dim3(nblocks), dim3(obs_threads()), 0, s, (const double2*)psi, w, nxy,
-                           part);
+    *nparts = mixed ? obs((const float2*)psi, w, nxy, part, s) : obs((const double2*)psi, w, nxy, part, s);
     return hipGetLastError();
 }
 
+template <class S>
+static int loss_lambda(const S* psi, S* lam, const double* w, const LossCoeffs& cf, int nxy, double* part,
+                       hipStream_t s) {
+    const dim3 g = pair_grid<S>(nxy);
+    auto fn = pair_k4<S>(nxy) ? k_loss_lambda<S, 4> : k_loss_lambda<S, 1>;
+    hipLaunchKernelGGL(fn, g, dim3(kPairThreads), 0, s, psi, lam, w, cf, nxy, part);
+    return blocks_of(g);
+}
 hipError_t launch_loss_lambda(const void* psi, void* lam, bool mixed, const double* w, const double* coeffs, int nxy,
-                              double* part, int nblocks, hipStream_t s) {
-    LossCoeffs cf{{coeffs[0], coeffs[1], coeffs[2], coeffs[3]}};
-    if (mixed)
-        hipLaunchKernelGGL(k_loss_lambda<float2>, dim3(nblocks), dim3(obs_threads()), 0, s, (const float2*)psi,
-                           (float2*)lam, w, cf, nxy, part);
-    else
-        hipLaunchKernelGGL(k_loss_lambda<double2>, dim3(nblocks), dim3(obs_threads()), 0, s, (const double2*)psi,
-                           (double2*)lam, w, cf, nxy, part);
+                              double* part, int* nparts, hipStream_t s) {
+    const LossCoeffs cf{{coeffs[0], coeffs[1], coeffs[2], coeffs[3]}};
+    *nparts = mixed ? loss_lambda((const float2*)psi, (float2*)lam, w, cf, nxy, part, s)
+                    : loss_lambda((const double2*)psi, (double2*)lam, w, cf, nxy, part, s);
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_parts(const double* part, int nparts, int width, double* out, hipStream_t s) {
+hipError_t launch_reduce_parts(const double* part, int nparts, int width, double* scratch, double* out,
+                               hipStream_t s) {
+    // one block per sum takes 256 parts per round of dependent loads; past 16 rounds a
+    // first stage of kReduceBlocks blocks pays for its launch (the reverse sweep's
+    // dL/dB: 65536 parts at 128x64, 90 -> 5 us)
+    if (nparts > 4096) {
+        if (width != 1) return hipErrorInvalidValue;  // scratch holds one sum per block
+        hipLaunchKernelGGL(k_reduce_parts, dim3(1, kReduceBlocks), dim3(256), 0, s, part, nparts, 1, scratch);
+        part = scratch;
+        nparts = kReduceBlocks;
+    }
     hipLaunchKernelGGL(k_reduce_parts, dim3(width), dim3(256), 0, s, part, nparts, width, out);
     return hipGetLastError();
 }
@@ -399,16 +557,6 @@ hipError_t launch_conditional(const void* psi, bool mixed, int nxy, int r2, doub
         hipLaunchKernelGGL(k_conditional<float2>, dim3(nb), dim3(256), 0, s, (const float2*)psi, nxy, r2, out);
     else
         hipLaunchKernelGGL(k_conditional<double2>, dim3(nb), dim3(256), 0, s, (const double2*)psi, nxy, r2, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_c128_to_c64(const double2* in, float2* out, int64_t count, hipStream_t s) {
-    hipLaunchKernelGGL(k_c128_to_c64, dim3(1024), dim3(256), 0, s, in, out, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_c64_to_c128(const float2* in, double2* out, int64_t count, hipStream_t s) {
-    hipLaunchKernelGGL(k_c64_to_c128, dim3(1024), dim3(256), 0, s, in, out, count);
     return hipGetLastError();
 }
 
@@ -451,7 +599,7 @@ double* scratch_on(int device) {
 hipError_t launch_grad_finish(const double* m_x2, int bpr_x2, const double* m_y2, int bpr_y2, const double* m_y1,
                               const double* m_x1, int nx, int ny, double gscale, double* dldv, hipStream_t s) {
     const int nxy = nx * ny;
-    hipLaunchKernelGGL(k_grad_finish, dim3((nxy + 255) / 256), dim3(256), 0, s, m_x2, bpr_x2, m_y2, bpr_y2, m_y1,
+    hipLaunchKernelGGL(k_grad_finish, dim3(nxy / kFinishEntries), dim3(256), 0, s, m_x2, bpr_x2, m_y2, bpr_y2, m_y1,
                        m_x1, nx, ny, gscale, dldv);
     return hipGetLastError();
 }
