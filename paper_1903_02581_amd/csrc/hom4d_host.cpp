@@ -232,7 +232,8 @@ struct hom4d {
     uint64_t v_hash = 0;         // FNV-1a of the last potential table (0: none)
     double norm_tol = 1e-6;
     int pass_plan = 0;           // 0: fused plane pass where built, 1: per-axis passes only
-    bool plane_built = false;    // a fused plane kernel exists for (nx, ny, precision)
+    bool plane_built = false;    // the three-pass plan exists for (nx, ny)
+    bool pair_built = false;     // the two fused plane kernels exist for (nx, ny, precision)
     // gradient recording
     bool rec = false;
     int ckpt_every = 0;
@@ -472,16 +473,15 @@ int run_pass(hom4d* h, int axis, KTab kt, int vmode, int nst, void* lam, bool re
     return sync_check(h, "axis pass");
 }
 
-// The fused (x2, y2) plane pass: X2(kt), potential factor, Y2(dt).
-int run_plane(hom4d* h, KTab kt) {
+// Arguments that the two fused plane passes share (ktab: the pass's x kinetic table).
+PassArgs plane_args(const hom4d* h, const double2* ktab) {
     const hom4d_cfg& c = h->cfg;
-    if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
     PassArgs a{};
     a.psi = h->psi;
     a.nx = c.nx;
     a.ny = c.ny;
     a.tw = h->tw_x;
-    a.ktab = kt == KX_HALF ? h->kxt_half : h->kxt_full;  // k-major
+    a.ktab = ktab;
     a.tw2 = h->tw_y;
     a.ktab2 = h->ky_full;
     a.a1 = h->a1_half;
@@ -494,11 +494,48 @@ int run_plane(hom4d* h, KTab kt) {
     a.soft2 = c.soft_nm * c.soft_nm;
     a.ck = c.coulomb_c * h->u.kc;
     a.inv_screen = c.screen_nm > 0.0 ? 1.0 / c.screen_nm : 0.0;
+    return a;
+}
+
+// The fused (x2, y2) plane pass: X2(kt), potential factor, Y2(dt).
+int run_plane(hom4d* h, KTab kt) {
+    const hom4d_cfg& c = h->cfg;
+    if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
+    const PassArgs a = plane_args(h, kt == KX_HALF ? h->kxt_half : h->kxt_full);  // k-major
     HIP_TRY(timed_launch(h, 4, [&] { return launch_plane(c.nx, c.ny, h->mixed, a, h->stream); }));
     return sync_check(h, "plane pass");
 }
 
+// The fused (x1, y1) plane pass: Y1(dt), potential factor, X1(kt).
+int run_plane1(hom4d* h, KTab kt) {
+    const hom4d_cfg& c = h->cfg;
+    if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
+    const PassArgs a = plane_args(h, kt == KX_HALF ? h->kx_half : h->kx_full);  // y-major
+    HIP_TRY(launch_plane1(c.nx, c.ny, h->mixed, a, h->stream));
+    return sync_check(h, "plane pass of electron 1");
+}
+
 bool use_plane(const hom4d* h) { return h->pass_plan == 0 && h->plane_built; }
+
+// Steps as the two plane passes where both are built, except while the passes are
+// timed one by one (they are reported by the kinds of the three- and four-pass
+// plans), and in a recorded complex64 run, which keeps the passes that its reverse
+// sweep undoes: there every pass rounds the state, and the fused one rounds it in other places.
+bool use_pair(const hom4d* h) {
+    return h->pass_plan == 0 && h->pair_built && !h->timing && !(h->mixed && h->rec);
+}
+
+// n whole forward steps in two passes per step:
+//   X1 | [X2, V, Y2] | [Y1, V, X1]  ...  closing X2 half.
+int run_steps_pair(hom4d* h, int64_t n) {
+    int rc;
+    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr))) return rc;
+    for (int64_t i = 0; i < n; ++i) {
+        if ((rc = run_plane(h, i == 0 ? KX_HALF : KX_FULL))) return rc;
+        if ((rc = run_plane1(h, i == n - 1 ? KX_HALF : KX_FULL))) return rc;
+    }
+    return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr);
+}
 
 // n whole forward steps in three passes per step:
 //   X1 | [X2, V, Y2] (plane) | [Y1, V]  ...  closing X1, X2 halves.
@@ -534,7 +571,8 @@ int run_steps_axis(hom4d* h, int64_t n) {
 // n whole steps with merged X halves; the state is closed at the end.
 int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradCtx* g) {
     if (n <= 0) return HOM4D_OK;
-    if (nst == 1 && !reverse) return use_plane(h) ? run_steps_plane(h, n) : run_steps_axis(h, n);
+    if (nst == 1 && !reverse)
+        return use_pair(h) ? run_steps_pair(h, n) : use_plane(h) ? run_steps_plane(h, n) : run_steps_axis(h, n);
     // reverse (dual-state) sweep: X1 | X2 | V, Y1 | Y2, V -- the gradient marginals of each
     // potential factor are taken by the passes on either side of it
     const bool gr = nst == 2;
@@ -837,7 +875,8 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
         fail(HOM4D_EHIP, "device scratch address: %s", hipGetErrorString(e));
         return cleanup(HOM4D_EHIP);
     }
-    h->plane_built = plane_available(nx, ny, h->mixed);
+    h->plane_built = plane_available(nx, ny);
+    h->pair_built = pair_available(nx, ny, h->mixed);
     *out = h;
     return HOM4D_OK;
 }

@@ -135,9 +135,20 @@ hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const Pa
 
 // Fused (x2, y2)-plane pass: X2(ktab) -> potential factor -> Y2(ktab2), one
 // workgroup per electron-1 position.  Returns hipErrorInvalidValue when no
-// kernel is built for (nx, ny, storage); plane_available() says beforehand.
-bool plane_available(int nx, int ny, bool mixed);
+// kernel is built for (nx, ny, storage).  plane_available(): the grids whose steps
+// are planned in three passes around it.
+bool plane_available(int nx, int ny);
 hipError_t launch_plane(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s);
+
+// Fused (x1, y1)-plane pass: Y1(ktab2) -> potential factor -> X1(ktab), launched on
+// tiles of w consecutive electron-2 positions.  pair_available(): both plane passes
+// are built, so that a step can run as the two.
+struct Plane1Launch {
+    int threads, w;
+    size_t lds;
+};
+bool pair_available(int nx, int ny, bool mixed);
+hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s);
 
 // Reductions and elementwise kernels over all pairs (r1, r2).  The reductions say
 // in *nparts how many partial sums (of their width) they write; at most

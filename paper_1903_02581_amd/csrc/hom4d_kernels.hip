@@ -42,6 +42,8 @@ AxisKernel pick_axis3_f64(int axis, int n, int vk, int nst, bool nt, bool pers, 
 AxisKernel pick_axis3_f32(int axis, int n, int vk, int nst, bool nt, bool pers, int w, int* t);
 AxisKernel pick_plane_f64(int nx, int ny, int vk, int* nt);
 AxisKernel pick_plane_f32(int nx, int ny, int vk, int* nt);
+AxisKernel pick_plane1_f64(int nx, int ny, int vk, Plane1Launch* p);
+AxisKernel pick_plane1_f32(int nx, int ny, int vk, Plane1Launch* p);
 
 namespace {
 
@@ -392,6 +394,21 @@ hipError_t resident_blocks(AxisKernel fn, int threads, size_t lds_bytes, int* ou
     return hipSuccess;
 }
 
+// Dynamic LDS above 64 KB has to be enabled per kernel, once.
+static hipError_t allow_lds(AxisKernel fn, size_t lds_bytes) {
+    if (lds_bytes <= 64 * 1024) return hipSuccess;
+    static std::mutex mu;
+    static std::unordered_set<const void*> raised;
+    std::lock_guard<std::mutex> lock(mu);
+    const void* key = reinterpret_cast<const void*>(fn);
+    if (!raised.count(key)) {
+        hipError_t e = hipFuncSetAttribute(key, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        raised.insert(key);
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const PassArgs& a, int64_t nlines,
                        size_t lds_bytes, hipStream_t s) {
     int t = 0;
@@ -419,18 +436,8 @@ hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const Pa
         const size_t need = axis_xchg_bytes(sh.n2 > 1 ? n : 0, a.W, nst, axis_xchg_c64(axis, mixed)) + 3u * (size_t)n * 16u;
         if (lds_bytes < need) return hipErrorInvalidValue;
     }
-    if (lds_bytes > 64 * 1024) {
-        // dynamic LDS above 64 KB has to be enabled per kernel, once
-        static std::mutex mu;
-        static std::unordered_set<const void*> raised;
-        std::lock_guard<std::mutex> lock(mu);
-        const void* key = reinterpret_cast<const void*>(fn);
-        if (!raised.count(key)) {
-            hipError_t e = hipFuncSetAttribute(key, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (e != hipSuccess) return e;
-            raised.insert(key);
-        }
-    }
+    hipError_t le = allow_lds(fn, lds_bytes);
+    if (le != hipSuccess) return le;
     int64_t grid = nblocks;
     if (pers) {
         // persistent pass: the blocks that fit the device at once walk the
@@ -445,9 +452,11 @@ hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const Pa
     return hipGetLastError();
 }
 
-bool plane_available(int nx, int ny, bool mixed) {
-    int nt = 0;
-    return (mixed ? pick_plane_f32(nx, ny, 1, &nt) : pick_plane_f64(nx, ny, 1, &nt)) != nullptr;
+bool plane_available(int nx, int ny) {
+    constexpr int sizes[][2] = {{16, 16}, {24, 24}, {32, 32}, {48, 48}, {64, 64}, {48, 16}, {16, 48}};
+    for (const auto& q : sizes)
+        if (nx == q[0] && ny == q[1]) return true;
+    return false;
 }
 
 hipError_t launch_plane(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s) {
@@ -456,6 +465,22 @@ hipError_t launch_plane(int nx, int ny, bool mixed, const PassArgs& a, hipStream
     AxisKernel fn = mixed ? pick_plane_f32(nx, ny, vk, &nt) : pick_plane_f64(nx, ny, vk, &nt);
     if (!fn || nt <= 0 || nt > 1024) return hipErrorInvalidValue;
     hipLaunchKernelGGL(fn, dim3((unsigned)(nx * ny)), dim3(nt), 0, s, a);
+    return hipGetLastError();
+}
+
+bool pair_available(int nx, int ny, bool mixed) {
+    Plane1Launch p{};
+    return (mixed ? pick_plane1_f32(nx, ny, 1, &p) : pick_plane1_f64(nx, ny, 1, &p)) != nullptr;
+}
+
+hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s) {
+    Plane1Launch p{};
+    const int vk = a.vdirect ? 2 : 1;
+    AxisKernel fn = mixed ? pick_plane1_f32(nx, ny, vk, &p) : pick_plane1_f64(nx, ny, vk, &p);
+    if (!fn || p.lds > 160 * 1024 || (nx * ny) % p.w != 0) return hipErrorInvalidValue;
+    hipError_t e = allow_lds(fn, p.lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(nx * ny / p.w)), dim3(p.threads), p.lds, s, a);
     return hipGetLastError();
 }
 

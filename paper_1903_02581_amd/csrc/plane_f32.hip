@@ -17,17 +17,14 @@ AxisKernel mk(int* nt, int vk) {
 }  // namespace
 
 // Plane sizes with a fused kernel: the FP64 LDS image (nx rows of ny + ny/8
-// slots) must fit in 160 KB with room for a second workgroup.
+// slots) must fit in 160 KB with room for a second workgroup.  The sizes of the
+// two-pass step, and 48x48 and 64x64, whose other passes stay per axis.
 AxisKernel pick_plane_f32(int nx, int ny, int vk, int* nt) {
 #define HOM4D_PLANE(X, Y) \
     if (nx == X && ny == Y) return mk<X, Y>(nt, vk);
-    HOM4D_PLANE(16, 16)
-    HOM4D_PLANE(24, 24)
-    HOM4D_PLANE(32, 32)
+    HOM4D_PAIR_SIZES
     HOM4D_PLANE(48, 48)
     HOM4D_PLANE(64, 64)
-    HOM4D_PLANE(48, 16)
-    HOM4D_PLANE(16, 48)
 #undef HOM4D_PLANE
     *nt = 0;
     return nullptr;

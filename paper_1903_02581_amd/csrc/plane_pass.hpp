@@ -39,11 +39,13 @@ template <> struct Shape<128> { static constexpr int n1 = 16, n2 = 8, t = 8; };
 // the y stage's row reads (8 lanes along each of two rows) and its sub-row
 // reads (stride 8 along two rows) all do at 64 x 64, where row = 72 puts the
 // two rows of a lane group half a bank cycle apart.
+// Rows of 12 (not whole groups of 8) are padded by one slot.
 template <int NY>
 struct PlaneLds {
-    static_assert(NY % 8 == 0, "plane rows are whole groups of 8");
-    static constexpr int row = NY + NY / 8;
-    __device__ static __forceinline__ int at(int r, int p) { return r * row + (p ^ ((p >> 3) & 7)); }
+    static constexpr int row = NY % 8 == 0 ? NY + NY / 8 : NY + 1;
+    __device__ static __forceinline__ int at(int r, int p) {
+        return r * row + (NY % 8 == 0 ? (p ^ ((p >> 3) & 7)) : p);
+    }
 };
 
 // One plane per workgroup, grid = nx * ny.  Barriers: one after every LDS write
@@ -351,6 +353,227 @@ __global__ void __launch_bounds__(NT) k_plane2(const PassArgs a) {
                     for (int n1 = 0; n1 < B1; ++n1) st<S>(base + row * NY + n1, u[n1]);
                 }
             }
+        }
+    }
+}
+
+// Fused pass over the strided (x1, y1) plane of W consecutive electron-2 positions.
+//
+// For fixed r2 the values Psi(x1, y1, r2) lie nx*ny apart; a workgroup takes W
+// consecutive r2 (runs of W elements) and applies, in one read and one write,
+//     Y1(dt), V(dt/2), X1(tau):
+// the three factors of the Strang step that follow the (x2, y2) plane pass, so that
+// the two plane passes make a whole step.  The operations on a line are those of
+// the per-axis passes in the same order: with complex128 storage the result is the same
+// bit for bit.
+//
+// A line's threads are W apart on consecutive lanes with W T | 64, so every
+// exchange of either stage stays inside one wavefront; the workgroup meets once, at the
+// hand-off from the y lines to the x lines.  LDS holds the W planes in the storage
+// type, position (x, y) of column w at (x NY + swizzle(x, y)) W + w: n2 = T for every
+// length, so the XOR moves a stage-B access (stride n2 along the line) of the T threads, and
+// the x lines' accesses (stride NY), onto T different bank groups.
+template <int NX, int NY>
+struct Plane1Lds {
+    static constexpr int A2 = Shape<NX>::n2, B2 = Shape<NY>::n2;
+    static_assert(Shape<NX>::t == A2 && Shape<NY>::t == B2, "a thread per column of the first factor");
+    static_assert(NY % A2 == 0 && NY % B2 == 0, "the XORs stay inside a row");
+    __device__ static __forceinline__ int at(int x, int y) {
+        return x * NY + (y ^ ((y / B2) % B2) ^ (x % A2) ^ ((x / A2) % A2));
+    }
+};
+
+constexpr int plane1_threads(int nx, int ny, int tx, int ty, int w) {
+    const int s = (ny * tx > nx * ty ? ny * tx : nx * ty) * w;
+    return ((s + 63) / 64) * 64;
+}
+
+// Columns per workgroup, and the grids whose step is two plane passes.  With four
+// columns a wavefront's accesses are 64-byte (complex128) or 32-byte runs; measured
+// per step against the three- or four-pass plan: 16x16 complex128 14.0 -> 8.9 us,
+// 24x24 27.3 -> 21.2, 32x32 45.9 -> 34.5, 48x16 31.3 -> 23.4, 32x24 42.2 -> 25.4,
+// complex64 33.1 -> 20.6 (launches and the latency of one short chain per kernel bound
+// them; two columns 26.7 and eight 27.7 us at 32x24 complex128).  Past 1024 points a
+// plane the runs cost more than the pass saved: 48x48 complex64 80.9 -> 83.7 us, 64x64
+// complex128 (two columns, all that fit) 281 -> 304.
+constexpr int kPlane1W = 4;
+#define HOM4D_PAIR_SIZES                                                                                       \
+    HOM4D_PLANE(8, 8) HOM4D_PLANE(8, 12) HOM4D_PLANE(8, 16) HOM4D_PLANE(8, 24) HOM4D_PLANE(8, 32)              \
+    HOM4D_PLANE(8, 48) HOM4D_PLANE(8, 64)                                                                      \
+    HOM4D_PLANE(12, 8) HOM4D_PLANE(12, 12) HOM4D_PLANE(12, 16) HOM4D_PLANE(12, 24) HOM4D_PLANE(12, 32)         \
+    HOM4D_PLANE(12, 48) HOM4D_PLANE(12, 64)                                                                    \
+    HOM4D_PLANE(16, 8) HOM4D_PLANE(16, 12) HOM4D_PLANE(16, 16) HOM4D_PLANE(16, 24) HOM4D_PLANE(16, 32)         \
+    HOM4D_PLANE(16, 48) HOM4D_PLANE(16, 64)                                                                    \
+    HOM4D_PLANE(24, 8) HOM4D_PLANE(24, 12) HOM4D_PLANE(24, 16) HOM4D_PLANE(24, 24) HOM4D_PLANE(24, 32)         \
+    HOM4D_PLANE(32, 8) HOM4D_PLANE(32, 12) HOM4D_PLANE(32, 16) HOM4D_PLANE(32, 24) HOM4D_PLANE(32, 32)         \
+    HOM4D_PLANE(48, 8) HOM4D_PLANE(48, 12) HOM4D_PLANE(48, 16) HOM4D_PLANE(64, 8) HOM4D_PLANE(64, 16)
+
+template <class S, int NX, int NY, int W, int VK>
+__global__ void __launch_bounds__(plane1_threads(NX, NY, Shape<NX>::t, Shape<NY>::t, W)) k_plane1(const PassArgs a) {
+    using SX_ = Shape<NX>;
+    using SY_ = Shape<NY>;
+    using LY = Plane1Lds<NX, NY>;
+    constexpr int NT = plane1_threads(NX, NY, SX_::t, SY_::t, W);
+    constexpr int A1 = SX_::n1, A2 = SX_::n2, TX = SX_::t, B1 = SY_::n1, B2 = SY_::n2, TY = SY_::t;
+    constexpr int EX = NX / TX, EY = NY / TY;
+    static_assert(NT <= 1024 && 64 % (W * TX) == 0 && 64 % (W * TY) == 0, "lines inside a wavefront");
+    using X = Xchg<S>;
+    extern __shared__ double2 lds_raw[];
+    typename X::T* L = reinterpret_cast<typename X::T*>(lds_raw);
+    double2* TW = reinterpret_cast<double2*>(reinterpret_cast<char*>(lds_raw) + sizeof(typename X::T) * NX * NY * W);
+    const double2* twx = TW;
+    const double2* twy = TW + NX;
+    const double2* ky = TW + NX + NY;
+
+    const int tid = threadIdx.x, w = tid % W;
+    constexpr int NXY = NX * NY;
+    // Each of the 8 XCDs takes a run of neighbouring tiles: tiles narrower than a
+    // 128-byte line then share it in that XCD's L2.
+    const int ntiles = NXY / W, per = ntiles / 8;
+    const int tile = (ntiles % 8 == 0) ? (blockIdx.x % 8) * per + blockIdx.x / 8 : blockIdx.x;
+    const int r2 = tile * W + w, i2 = r2 / NY, j2 = r2 % NY;
+    S* base = reinterpret_cast<S*>(a.psi) + r2;
+
+    auto wave_sync = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+    auto at = [&](int x, int y) { return LY::at(x, y) * W + w; };
+
+    // ---------------- Y1 stage: line (x1, w), threads t along y1
+    const int ty = (tid / W) % TY, x1 = tid / (W * TY);
+    const bool on_y = x1 < NX;
+    S raw[EY];
+    if (on_y) {
+#pragma unroll
+        for (int e = 0; e < EY; ++e) raw[e] = ld_raw<S, false>(base + (int64_t)(x1 * NY + (e % B1) * B2 + ty + TY * (e / B1)) * NXY);
+    }
+    for (int i = tid; i < NX + 2 * NY; i += NT) TW[i] = i < NX ? a.tw[i] : i < NX + NY ? a.tw2[i - NX] : a.ktab2[i - NX - NY];
+    __syncthreads();
+    if (on_y) {
+        double2 v[EY];
+#pragma unroll
+        for (int e = 0; e < EY; ++e) v[e] = widen(raw[e]);
+        constexpr int JA = B2 / TY, IB = B1 / TY;
+#pragma unroll
+        for (int jj = 0; jj < JA; ++jj) {
+            dft<B1, -1>(&v[jj * B1]);
+            if constexpr (B2 > 1) {
+                const int jc = ty + TY * jj;
+#pragma unroll
+                for (int k1 = 1; k1 < B1; ++k1) v[jj * B1 + k1] = cmul(v[jj * B1 + k1], twy[(jc * k1) % NY]);
+#pragma unroll
+                for (int k1 = 0; k1 < B1; ++k1) L[at(x1, k1 * B2 + jc)] = X::put(v[jj * B1 + k1]);
+            }
+        }
+        if constexpr (B2 > 1) {
+            wave_sync();
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii) {
+#pragma unroll
+                for (int j = 0; j < B2; ++j) v[ii * B2 + j] = X::get(L[at(x1, (ty + TY * ii) * B2 + j)]);
+                dft<B2, -1>(&v[ii * B2]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EY; ++e) v[e] = cmul(v[e], ky[ty + TY * (e / B2) + B1 * (e % B2)]);
+        if constexpr (B2 > 1) {
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii) {
+                dft<B2, 1>(&v[ii * B2]);
+#pragma unroll
+                for (int j = 0; j < B2; ++j) L[at(x1, (ty + TY * ii) * B2 + j)] = X::put(v[ii * B2 + j]);
+            }
+            wave_sync();
+#pragma unroll
+            for (int jj = 0; jj < JA; ++jj)
+#pragma unroll
+                for (int k1 = 0; k1 < B1; ++k1) v[jj * B1 + k1] = X::get(L[at(x1, k1 * B2 + ty + TY * jj)]);
+        }
+#pragma unroll
+        for (int jj = 0; jj < JA; ++jj) {
+            if constexpr (B2 > 1) {
+#pragma unroll
+                for (int k1 = 1; k1 < B1; ++k1) v[jj * B1 + k1] = cmulc(v[jj * B1 + k1], twy[((ty + TY * jj) * k1) % NY]);
+            }
+            dft<B1, 1>(&v[jj * B1]);
+        }
+        // potential factor at (x1, y1 = (e % B1) B2 + t + TY (e / B1)), as the y1 line pass applies it
+        if constexpr (VK == 1) {
+            const double2 f2 = a.a1[r2];
+            batched<EY, 4>(
+                [&](int e) {
+                    const int y = (e % B1) * B2 + ty + TY * (e / B1);
+                    VLoad l;
+                    l.p = a.a1[x1 * NY + y];
+                    l.r = a.ac[(x1 - i2 + NX - 1) * (2 * NY - 1) + (y - j2 + NY - 1)];
+                    return l;
+                },
+                [&](int e, const VLoad& l) { v[e] = cmul(v[e], cmul(cmul(l.p, f2), l.r)); });
+        } else {
+            batched<EY, 8>(
+                [&](int e) { return vload<2>(a, x1, (e % B1) * B2 + ty + TY * (e / B1), i2, j2); },
+                [&](int e, const VLoad& l) {
+                    v[e] = cmul(v[e], vcombine<2, false>(a, l, x1, (e % B1) * B2 + ty + TY * (e / B1), i2, j2));
+                });
+        }
+#pragma unroll
+        for (int e = 0; e < EY; ++e) L[at(x1, (e % B1) * B2 + ty + TY * (e / B1))] = X::put(v[e]);
+    }
+    __syncthreads();
+
+    // ---------------- X1 stage: line (y1, w), threads t along x1
+    const int tx = (tid / W) % TX, y1 = tid / (W * TX);
+    if (y1 < NY) {
+        constexpr int JA = A2 / TX, IB = A1 / TX;
+        double2 v[EX], kf[EX];
+        const double2* kt = a.ktab + y1 * NX;  // y-major: the line's row of wave numbers
+#pragma unroll
+        for (int e = 0; e < EX; ++e) kf[e] = kt[tx + TX * (e / A2) + A1 * (e % A2)];
+#pragma unroll
+        for (int jj = 0; jj < JA; ++jj) {
+            const int jc = tx + TX * jj;
+#pragma unroll
+            for (int n1 = 0; n1 < A1; ++n1) v[jj * A1 + n1] = X::get(L[at(n1 * A2 + jc, y1)]);
+            dft<A1, -1>(&v[jj * A1]);
+            if constexpr (A2 > 1) {
+#pragma unroll
+                for (int k1 = 1; k1 < A1; ++k1) v[jj * A1 + k1] = cmul(v[jj * A1 + k1], twx[(jc * k1) % NX]);
+#pragma unroll
+                for (int k1 = 0; k1 < A1; ++k1) L[at(k1 * A2 + jc, y1)] = X::put(v[jj * A1 + k1]);
+            }
+        }
+        if constexpr (A2 > 1) {
+            wave_sync();
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii) {
+#pragma unroll
+                for (int j = 0; j < A2; ++j) v[ii * A2 + j] = X::get(L[at((tx + TX * ii) * A2 + j, y1)]);
+                dft<A2, -1>(&v[ii * A2]);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < EX; ++e) v[e] = cmul(v[e], kf[e]);
+        if constexpr (A2 > 1) {
+#pragma unroll
+            for (int ii = 0; ii < IB; ++ii) {
+                dft<A2, 1>(&v[ii * A2]);
+#pragma unroll
+                for (int j = 0; j < A2; ++j) L[at((tx + TX * ii) * A2 + j, y1)] = X::put(v[ii * A2 + j]);
+            }
+            wave_sync();
+#pragma unroll
+            for (int jj = 0; jj < JA; ++jj)
+#pragma unroll
+                for (int k1 = 0; k1 < A1; ++k1) v[jj * A1 + k1] = X::get(L[at(k1 * A2 + tx + TX * jj, y1)]);
+        }
+#pragma unroll
+        for (int jj = 0; jj < JA; ++jj) {
+            const int jc = tx + TX * jj;
+            if constexpr (A2 > 1) {
+#pragma unroll
+                for (int k1 = 1; k1 < A1; ++k1) v[jj * A1 + k1] = cmulc(v[jj * A1 + k1], twx[(jc * k1) % NX]);
+            }
+            dft<A1, 1>(&v[jj * A1]);
+#pragma unroll
+            for (int n1 = 0; n1 < A1; ++n1) st<S>(base + (int64_t)((n1 * A2 + jc) * NY + y1) * NXY, v[jj * A1 + n1]);
         }
     }
 }
