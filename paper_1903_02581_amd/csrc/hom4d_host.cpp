@@ -119,6 +119,16 @@ int64_t ilog2_pow2_divisor(int64_t v) {  // largest power of two dividing v
     return v & (-v);
 }
 
+// Lines of an x2 block: a part of one y2 row, so that its accesses are whole runs and
+// (gradient partials) its lines share r1.  Forward passes let blocks run over row ends where
+// the row's largest power of two is 4 or less, which would leave blocks of half a
+// wavefront: x2+V at 128x12 complex128 28.2 -> 21.5 us, 128x6 20.9 -> 15.7, 256x12 complex64
+// 68.6 -> 52.1; at 8 (ny = 24) it changes nothing, at 16 (64x48) 50.6 -> 52.9.
+int64_t x2_lines(int ny, bool grad) {
+    const int64_t d = ilog2_pow2_divisor(ny);
+    return grad || d > 4 ? d : 1 << 20;
+}
+
 AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
     AxisPlan p{};
     p.n = (axis == AX_X1 || axis == AX_X2) ? nx : ny;
@@ -148,7 +158,7 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         // y1: 4.28 -> 3.83 ms; 128 x 96 x1: 0.559 -> 0.526 ms).
         int64_t w = axis3_nominal_w(axis, p.n, t3, nst, mixed);
         w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
-        if (axis == AX_X2) w = std::min<int64_t>(w, ilog2_pow2_divisor(ny));
+        if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad));
         if (axis == AX_Y2 && grad) w = std::min<int64_t>(w, ilog2_pow2_divisor(nx));
         p.W = (int)std::max<int64_t>(w, 1);
         // persistent form on the complex64 x1 and y1 passes of 128- and 256-point
@@ -176,7 +186,7 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         while (w > cap) w >>= 1;
     }
     w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
-    if (axis == AX_X2) w = std::min<int64_t>(w, ilog2_pow2_divisor(ny));
+    if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad));
     if (axis == AX_Y2 && grad) w = std::min<int64_t>(w, ilog2_pow2_divisor(nx));
     if (axis == AX_Y1) w = std::min<int64_t>(w, ilog2_pow2_divisor(nxy));  // a block's lines share x1
     if (w < 1) w = 1;

@@ -1,5 +1,6 @@
 """Steps as two fused plane passes, at every grid that has both, against the four
-per-axis passes.
+per-axis passes; and the forward x2 pass where a block's lines run over the end of a
+y2 row, against the oracle.
 
 Tolerances: complex128, the same factors in another order over 3 steps, 1e-13 as for the
 three-pass plan; complex64, at most 11 roundings of 2^-24 a step in either plan, added up
@@ -11,7 +12,7 @@ import numpy as np
 import pytest
 
 from workloads.presets import build
-from tests.gpu_util import announce, rel_l2
+from tests.gpu_util import announce, oracle_run, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +62,16 @@ def test_recorded_complex64_run_keeps_its_passes():
     p.step(2)
     assert np.array_equal(p.store_state(), recorded)
     p.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(96, 24), (128, 6), (48, 24), (64, 12), (256, 12), (96, 6), (24, 4)])
+def test_x2_blocks_over_row_ends(nx, ny):
+    w = workload(nx, ny, 2)
+    announce(f"x2 blocks {nx}x{ny}")
+    from paper_1903_02581_amd import Propagator
+    ref, _ = oracle_run(w, 2)
+    for precision, tol in (("fp64", 1e-10), ("mixed", 5e-6)):
+        p = Propagator.from_workload(w, precision=precision)
+        p.step(2)
+        assert rel_l2(p.store_state(), ref) <= tol
+        p.close()
