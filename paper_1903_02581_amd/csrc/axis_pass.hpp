@@ -7,7 +7,9 @@
 #include <cstdint>
 
 #include "dft_regs.hpp"
+#include "estimates.hpp"
 #include "hom4d_internal.hpp"
+#include "phase.hpp"
 
 namespace hom4d_impl {
 namespace dev {
@@ -105,17 +107,6 @@ __device__ __forceinline__ double2 conjd(double2 a) { return make_double2(a.x, -
 // Im(conj(l) * p)
 __device__ __forceinline__ double im_cl_p(double2 l, double2 p) { return fma(l.x, p.y, -l.y * p.x); }
 
-// theta - 2 pi * rint(theta / 2 pi), 2 pi split in three parts (Cody & Waite);
-// the first part has 9 significant bits, so q * c1 is exact for |q| < 2^44.
-__device__ __forceinline__ double reduce_2pi(double th) {
-    const double inv2pi = 0.15915494309189535;
-    const double c1 = 6.28125;
-    const double c2 = 0.001935307179586477;
-    const double c3 = -1.0033115225336665e-19;
-    const double q = rint(th * inv2pi);
-    return fma(-q, c3, fma(-q, c2, fma(-q, c1, th)));
-}
-
 // Every load of a batch is issued before any of its values is used.  Left
 // alone, the machine scheduler places each loaded value's first use right after
 // its load, behind a wait for that load (s_waitcnt vmcnt(0)), so a wave keeps a
@@ -163,7 +154,7 @@ __device__ __forceinline__ VLoad vload(const PassArgs& a, int i1, int j1, int i2
 
 // exp(-i tau (V(r1) + V(r2) + V12(r1 - r2)) / hbar), or its conjugate, from the
 // loaded entries.  VK = 1: product of the one-body and two-body factor tables;
-// VK = 2: the FP64 angle evaluated here, reduced mod 2 pi, then sincos; VK = 3:
+// VK = 2: the FP64 angle evaluated here and its phase (phase.hpp); VK = 3:
 // as VK = 1 without the one-body factor of electron 1 (applied by the caller).
 template <int VK, bool CONJ>
 __device__ __forceinline__ double2 vcombine(const PassArgs& a, const VLoad& l, int i1, int j1, int i2, int j2) {
@@ -179,14 +170,11 @@ __device__ __forceinline__ double2 vcombine(const PassArgs& a, const VLoad& l, i
             const double ddx = (double)(i1 - i2) * a.dx;
             const double ddy = (double)(j1 - j2) * a.dy;
             const double r2 = ddx * ddx + ddy * ddy;
-            double vc = a.ck / sqrt(r2 + a.soft2);
+            double vc = a.ck * rsqrt_of(r2 + a.soft2);
             if (a.inv_screen > 0.0) vc *= exp(-sqrt(r2) * a.inv_screen);
             v += vc;
         }
-        const double th = reduce_2pi(a.vscale * v);  // vscale carries the sign of tau
-        double s, c;
-        sincos(th, &s, &c);
-        f = make_double2(c, -s);
+        f = expmi(a.vscale * v);  // vscale carries the sign of tau
     }
     return f;
 }

@@ -32,10 +32,13 @@
 #include <type_traits>
 
 #include "dft_regs.hpp"
+#include "estimates.hpp"
 
 namespace hom4d_impl {
 namespace eig {
 using namespace hom4d_dev;
+using dev::rcp_of;
+using dev::rsqrt_of;
 
 constexpr int kRegMax = 128;  // largest matrix held in registers
 constexpr int kMax = 256;     // largest matrix
@@ -72,20 +75,6 @@ __device__ __forceinline__ double2 msubr(double s, double2 a, double2 c) {
 // Re(conj(a) b)
 __device__ __forceinline__ double redot(double a, double b) { return a * b; }
 __device__ __forceinline__ double redot(double2 a, double2 b) { return fma(a.x, b.x, a.y * b.y); }
-
-// 1 / sqrt(x) and 1 / x for normal x > 0: the hardware estimates and two Newton steps
-__device__ __forceinline__ double rsqrt_of(double x) {
-    const double h = 0.5 * x;
-    double r = __builtin_amdgcn_rsq(x);
-    r *= fma(-h * r, r, 1.5);
-    r *= fma(-h * r, r, 1.5);
-    return r;
-}
-__device__ __forceinline__ double rcp_of(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
-}
 
 // the value of the lane that the DPP control names (within 16 lanes)
 constexpr int kXor15 = 0x140, kXor7 = 0x141, kXor3 = 0x1B, kXor1 = 0xB1;  // mirror, half mirror, quad_perm
