@@ -954,7 +954,7 @@ int hom4d_init_state(hom4d* h, const double* psi_a, const double* psi_b, int32_t
     HIP_TRY(hipMemcpyAsync(h->orb_dev, psi_a, nb, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(h->orb_dev + h->nxy, psi_b, nb, hipMemcpyHostToDevice, h->stream));
     int nparts = 0;
-    HIP_TRY(launch_init_norm(h->orb_dev, h->orb_dev + h->nxy, sym, h->nxy, h->red_part, &nparts, h->stream));
+    HIP_TRY(launch_init_norm(h->orb_dev, h->orb_dev + h->nxy, h->mixed, sym, h->nxy, h->red_part, &nparts, h->stream));
     double nrm = 0.0;
     int rc = fetch_reduction(h, nparts, 1, &nrm);
     if (rc) return rc;

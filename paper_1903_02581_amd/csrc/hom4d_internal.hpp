@@ -154,8 +154,8 @@ hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStrea
 // in *nparts how many partial sums (of their width) they write; at most
 // reduction_parts(nxy, mixed).
 int reduction_parts(int nxy, bool mixed);
-hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part, int* nparts,
-                            hipStream_t s);
+hipError_t launch_init_norm(const double2* pa, const double2* pb, bool mixed, int sym, int nxy, double* part,
+                            int* nparts, hipStream_t s);
 hipError_t launch_init_write(void* psi, bool mixed, const double2* pa, const double2* pb, int sym,
                              int nxy, double scale, hipStream_t s);
 hipError_t launch_obs(const void* psi, bool mixed, const double* w, int nxy, double* part, int* nparts,

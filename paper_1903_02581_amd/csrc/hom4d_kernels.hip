@@ -135,6 +135,26 @@ __global__ void __launch_bounds__(kPairThreads) k_init_norm(const double2* pa, c
     if (threadIdx.x == 0) part[blockIdx.y * gridDim.x + blockIdx.x] = s;
 }
 
+// The same norm for complex64 states, rows r1 over blocks and r2 over threads.  Its
+// last bit sets the last bit of every initial value, a few of which then round to the other
+// complex64 neighbour, and within a step or two the rounding of every pass follows: a
+// complex64 run is reproducible only with this order of summation.  It re-reads the
+// orbitals for every pair (128x64 108 us against 57, 256x128 1.55 ms against 0.77).
+constexpr int kNormRows = 1024;
+__global__ void k_init_norm_rows(const double2* pa, const double2* pb, int sym, int nxy, double* part) {
+    __shared__ double red[256];
+    double acc = 0.0;
+    for (int r1 = blockIdx.x; r1 < nxy; r1 += gridDim.x) {
+        const double2 a1 = pa[r1], b1 = pb[r1];
+        for (int r2 = threadIdx.x; r2 < nxy; r2 += blockDim.x) {
+            const double2 p = pair_value(a1, b1, pa[r2], pb[r2], sym);
+            acc += p.x * p.x + p.y * p.y;
+        }
+    }
+    const double s = block_sum(acc, red);
+    if (threadIdx.x == 0) part[blockIdx.x] = s;
+}
+
 template <class S, int K>
 __global__ void __launch_bounds__(kPairThreads) k_init_write(S* psi, const double2* pa, const double2* pb, int sym,
                                                              int nxy, double scale) {
@@ -485,11 +505,17 @@ hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStrea
 }
 
 int reduction_parts(int nxy, bool mixed) {
-    return std::max(blocks_of(pair_grid<double2>(nxy)), mixed ? blocks_of(pair_grid<float2>(nxy)) : 0);
+    return mixed ? std::max(std::min(nxy, kNormRows), blocks_of(pair_grid<float2>(nxy)))
+                 : blocks_of(pair_grid<double2>(nxy));
 }
 
-hipError_t launch_init_norm(const double2* pa, const double2* pb, int sym, int nxy, double* part, int* nparts,
-                            hipStream_t s) {
+hipError_t launch_init_norm(const double2* pa, const double2* pb, bool mixed, int sym, int nxy, double* part,
+                            int* nparts, hipStream_t s) {
+    if (mixed) {
+        *nparts = std::min(nxy, kNormRows);
+        hipLaunchKernelGGL(k_init_norm_rows, dim3(*nparts), dim3(256), 0, s, pa, pb, sym, nxy, part);
+        return hipGetLastError();
+    }
     const dim3 g = pair_grid<double2>(nxy);
     *nparts = blocks_of(g);
     auto fn = pair_k4<double2>(nxy) ? k_init_norm<4> : k_init_norm<1>;
