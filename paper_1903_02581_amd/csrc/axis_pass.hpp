@@ -293,9 +293,19 @@ struct LineGeom {
     }
 };
 
+// Least wavefronts per SIMD the compiler plans for (0: its own choice).  The reverse
+// sweep's passes with twelve elements a thread and state run a few registers past 256
+// and would leave one: two cost up to 26 spills.  48-point lines: y1 complex128 76.2 -> 68.8 us,
+// complex64 storage 60.9 -> 44.6, x2 complex64 55.7 -> 44.5; 24-point x2 22.6 -> 19.0.
+// Where the states share an exchange area the registers fit (x1) or the spills
+// cost more (x2 complex128 61.4 -> 67.9); three for eight elements (64-point lines) x1 226 -> 290.
+constexpr int axis_min_waves(int axis, int n, int e, int nst, bool c64) {
+    return nst == 2 && e >= 12 && !axis_one_area(axis, n, nst, c64) ? 2 : 0;
+}
+
 // VK: 0 = no potential factor on this pass, 1 = table form, 2 = per-point form.
 template <class S, int AXIS, int N1, int N2, int T, int NST, int VK, bool NT>
-__global__ void __launch_bounds__(256) k_axis(const PassArgs a) {
+__global__ void __launch_bounds__(256, axis_min_waves(AXIS, N1 * N2, N1 * N2 / T, NST, axis_xchg_c64(AXIS, !std::is_same<S, double2>::value))) k_axis(const PassArgs a) {
     constexpr int N = N1 * N2;
     constexpr int E = N / T;
     constexpr int JA = N2 / T;  // stage-A columns per thread
@@ -336,7 +346,7 @@ __global__ void __launch_bounds__(256) k_axis(const PassArgs a) {
     // table row: staged after the kinetic factor instead of read per element.
     constexpr bool A1_LDS = (AXIS == AX_Y1 && VK == 1);
     double2* TWL = reinterpret_cast<double2*>(reinterpret_cast<char*>(lds_raw) +
-                                              axis_xchg_bytes(N2 > 1 ? N : 0, W, NST, sizeof(typename X::T) == 8));
+                                              axis_xchg_bytes(AXIS, N2 > 1 ? N : 0, W, NST, sizeof(typename X::T) == 8));
     const int a1_row = A1_LDS ? (int)((blk * (uint32_t)W) / ((uint32_t)a.nx * (uint32_t)a.ny)) * a.ny : 0;
     for (int i = tid; i < (KT_LDS ? 2 * N : N) + (A1_LDS ? N : 0); i += T * W) {
         double2 v;
@@ -434,21 +444,37 @@ __global__ void __launch_bounds__(256) k_axis(const PassArgs a) {
     }
 
     const int LS = W + 1;  // padded LDS row (complex elements) for one position across W lines
+    // the two states of the reverse sweep share one exchange area or have one each
+    constexpr bool ONE = axis_one_area(AXIS, N, NST, sizeof(typename X::T) == 8);
+    auto slot = [&](int s, int p) -> typename X::T& { return lds[((ONE ? 0 : s * N) + p) * LS + cl]; };
     if constexpr (N2 > 1) {
-#pragma unroll
-        for (int s = 0; s < NST; ++s)
+        auto write_a = [&](int s) {
 #pragma unroll
             for (int jj = 0; jj < JA; ++jj)
 #pragma unroll
-                for (int k1 = 0; k1 < N1; ++k1)
-                    lds[(s * N + k1 * N2 + t + T * jj) * LS + cl] = X::put(v[s][jj * N1 + k1]);
-        line_sync<AXIS, T>();
-#pragma unroll
-        for (int s = 0; s < NST; ++s)
+                for (int k1 = 0; k1 < N1; ++k1) slot(s, k1 * N2 + t + T * jj) = X::put(v[s][jj * N1 + k1]);
+        };
+        auto read_b = [&](int s) {
 #pragma unroll
             for (int ii = 0; ii < IB; ++ii)
 #pragma unroll
-                for (int j = 0; j < N2; ++j) v[s][ii * N2 + j] = X::get(lds[(s * N + (t + T * ii) * N2 + j) * LS + cl]);
+                for (int j = 0; j < N2; ++j) v[s][ii * N2 + j] = X::get(slot(s, (t + T * ii) * N2 + j));
+        };
+        if constexpr (ONE) {
+#pragma unroll
+            for (int s = 0; s < NST; ++s) {
+                if (s > 0) line_sync<AXIS, T>();
+                write_a(s);
+                line_sync<AXIS, T>();
+                read_b(s);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NST; ++s) write_a(s);
+            line_sync<AXIS, T>();
+#pragma unroll
+            for (int s = 0; s < NST; ++s) read_b(s);
+        }
         // stage B: DFT_n2 over the columns; element (ii, k2) is wave number k1 + n1 * k2
 #pragma unroll
         for (int s = 0; s < NST; ++s)
@@ -503,21 +529,35 @@ __global__ void __launch_bounds__(256) k_axis(const PassArgs a) {
         for (int s = 0; s < NST; ++s)
 #pragma unroll
             for (int ii = 0; ii < IB; ++ii) dft<N2, 1>(&v[s][ii * N2]);
-        // each thread writes back exactly the positions it read for stage B: no barrier needed
-#pragma unroll
-        for (int s = 0; s < NST; ++s)
+        // each thread writes back exactly the positions it read for stage B (in one area: of
+        // the state it read last): no barrier needed
+        auto write_b = [&](int s) {
 #pragma unroll
             for (int ii = 0; ii < IB; ++ii)
 #pragma unroll
-                for (int j = 0; j < N2; ++j) lds[(s * N + (t + T * ii) * N2 + j) * LS + cl] = X::put(v[s][ii * N2 + j]);
-        line_sync<AXIS, T>();
-#pragma unroll
-        for (int s = 0; s < NST; ++s)
+                for (int j = 0; j < N2; ++j) slot(s, (t + T * ii) * N2 + j) = X::put(v[s][ii * N2 + j]);
+        };
+        auto read_a = [&](int s) {
 #pragma unroll
             for (int jj = 0; jj < JA; ++jj)
 #pragma unroll
-                for (int k1 = 0; k1 < N1; ++k1)
-                    v[s][jj * N1 + k1] = X::get(lds[(s * N + k1 * N2 + t + T * jj) * LS + cl]);
+                for (int k1 = 0; k1 < N1; ++k1) v[s][jj * N1 + k1] = X::get(slot(s, k1 * N2 + t + T * jj));
+        };
+        if constexpr (ONE) {
+#pragma unroll
+            for (int s = NST - 1; s >= 0; --s) {
+                write_b(s);
+                line_sync<AXIS, T>();
+                read_a(s);
+                if (s > 0) line_sync<AXIS, T>();
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < NST; ++s) write_b(s);
+            line_sync<AXIS, T>();
+#pragma unroll
+            for (int s = 0; s < NST; ++s) read_a(s);
+        }
     }
 #pragma unroll
     for (int s = 0; s < NST; ++s) {

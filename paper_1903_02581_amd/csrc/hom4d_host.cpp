@@ -182,7 +182,8 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         // for complex64 (W = 32 on n = 128), whose blocks then take half of it
         // since they exchange complex64
         const int64_t budget = mixed ? 81920 : 65536;
-        const int64_t cap = (budget - 3 * p.n * 16) / ((int64_t)nst * p.n * 16) - 1;
+        const int64_t areas = axis_one_area(axis, p.n, nst, axis_xchg_c64(axis, mixed)) ? 1 : nst;
+        const int64_t cap = (budget - 3 * p.n * 16) / (areas * p.n * 16) - 1;
         while (w > cap) w >>= 1;
     }
     w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
@@ -194,7 +195,7 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
     // exchange area, then the staged twiddles, kinetic factor and (y1) one-body
     // factor row (3n entries); the dual-state reduction scratch reuses the start
     // of the allocation at the end
-    const size_t ex = axis_xchg_bytes(sh.n2 > 1 ? p.n : 0, p.W, nst, axis_xchg_c64(axis, mixed));
+    const size_t ex = axis_xchg_bytes(axis, sh.n2 > 1 ? p.n : 0, p.W, nst, axis_xchg_c64(axis, mixed));
     const size_t red = nst == 2 ? (size_t)sh.t * p.W * sizeof(double) : 0;
     p.lds = std::max(ex + (size_t)3 * p.n * sizeof(double2), red);
     return p;

@@ -106,10 +106,20 @@ __host__ __device__ constexpr int axis3_nominal_w(int axis, int n, int t3, int n
 // complex64 storage: every axis but x1).
 __host__ __device__ constexpr bool axis_xchg_c64(int axis, bool mixed) { return mixed && axis != AX_X1; }
 
-// Exchange area of the two-stage kernel: nst states x n positions x (W + 1)
+// Whether the reverse sweep's two states take turns in one exchange area of the
+// two-stage kernel (more barriers, half the LDS, so more blocks per CU), complex128 entries
+// only.  Measured per pass: 48-point lines x1 complex64 storage 55.5 -> 45.2 us, complex128 66.9
+// -> 65.5, x2 complex128 65.9 -> 61.4, but y1 76.2 -> 81.3; 64-point lines y1 complex128 64x64
+// 219 -> 202, 128x64 866 -> 795, but x1 213 -> 241 and y2 194 -> 200.
+__host__ __device__ constexpr bool axis_one_area(int axis, int n, int nst, bool c64) {
+    return nst == 2 && !c64 && ((n == 48 && (axis == AX_X1 || axis == AX_X2)) || (n == 64 && axis == AX_Y1));
+}
+
+// Exchange area of the two-stage kernel: states at a time x n positions x (W + 1)
 // slots (n = 0 where the line needs no exchange), entries as above.
-__host__ __device__ constexpr size_t axis_xchg_bytes(int n, int w, int nst, bool c64) {
-    return ((size_t)nst * (size_t)n * (size_t)(w + 1) * (c64 ? 8u : 16u) + 15u) / 16u * 16u;
+__host__ __device__ constexpr size_t axis_xchg_bytes(int axis, int n, int w, int nst, bool c64) {
+    const size_t states = axis_one_area(axis, n, nst, c64) ? 1u : (size_t)nst;
+    return (states * (size_t)n * (size_t)(w + 1) * (c64 ? 8u : 16u) + 15u) / 16u * 16u;
 }
 
 // LDS of the three-stage kernel: the exchange area (nst states x n positions x

@@ -453,7 +453,7 @@ hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const Pa
     } else {
         FftShape sh;
         if (!fft_shape(n, &sh)) return hipErrorInvalidValue;
-        const size_t need = axis_xchg_bytes(sh.n2 > 1 ? n : 0, a.W, nst, axis_xchg_c64(axis, mixed)) + 3u * (size_t)n * 16u;
+        const size_t need = axis_xchg_bytes(axis, sh.n2 > 1 ? n : 0, a.W, nst, axis_xchg_c64(axis, mixed)) + 3u * (size_t)n * 16u;
         if (lds_bytes < need) return hipErrorInvalidValue;
     }
     hipError_t le = allow_lds(fn, lds_bytes);
