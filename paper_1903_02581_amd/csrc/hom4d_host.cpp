@@ -244,6 +244,7 @@ struct hom4d {
     double norm_tol = 1e-6;
     int pass_plan = 0;           // 0: fused plane pass where built, 1: per-axis passes only
     bool plane_built = false;    // the three-pass plan exists for (nx, ny)
+    bool regs_built = false;     // a register-held plane kernel exists (complex128, table form)
     bool pair_built = false;     // the two fused plane kernels exist for (nx, ny, precision)
     // gradient recording
     bool rec = false;
@@ -517,6 +518,16 @@ int run_plane(hom4d* h, KTab kt) {
     return sync_check(h, "plane pass");
 }
 
+// The (x2, y2) plane pass with the plane in registers.
+int run_plane_regs(hom4d* h, KTab kt) {
+    const hom4d_cfg& c = h->cfg;
+    if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
+    PassArgs a = plane_args(h, kt == KX_HALF ? h->kxt_half : h->kxt_full);  // k-major
+    a.nt = h->state_bytes > (size_t(1) << 30) ? 1 : 0;  // as the line passes (run_pass)
+    HIP_TRY(launch_plane_regs(c.nx, c.ny, a, h->stream));
+    return sync_check(h, "plane pass in registers");
+}
+
 // The fused (x1, y1) plane pass: Y1(dt), potential factor, X1(kt).
 int run_plane1(hom4d* h, KTab kt) {
     const hom4d_cfg& c = h->cfg;
@@ -548,6 +559,11 @@ int run_steps_pair(hom4d* h, int64_t n) {
     return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr);
 }
 
+// Steps in three passes around the register-held plane pass, with the same exceptions.
+bool use_plane_regs(const hom4d* h) {
+    return h->pass_plan == 0 && h->regs_built && !h->timing;
+}
+
 // n whole forward steps in three passes per step:
 //   X1 | [X2, V, Y2] (plane) | [Y1, V]  ...  closing X1, X2 halves.
 int run_steps_plane(hom4d* h, int64_t n) {
@@ -555,7 +571,8 @@ int run_steps_plane(hom4d* h, int64_t n) {
     if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr))) return rc;
     for (int64_t i = 0; i < n; ++i) {
         const bool last = i == n - 1;
-        if ((rc = run_plane(h, i == 0 ? KX_HALF : KX_FULL))) return rc;
+        const KTab kx = i == 0 ? KX_HALF : KX_FULL;
+        if ((rc = use_plane_regs(h) ? run_plane_regs(h, kx) : run_plane(h, kx))) return rc;
         if ((rc = run_pass(h, AX_Y1, KY_FULL, 2, 1, nullptr, false, 0, nullptr))) return rc;
         if ((rc = run_pass(h, AX_X1, last ? KX_HALF : KX_FULL, 0, 1, nullptr, false, 0, nullptr))) return rc;
     }
@@ -583,7 +600,9 @@ int run_steps_axis(hom4d* h, int64_t n) {
 int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradCtx* g) {
     if (n <= 0) return HOM4D_OK;
     if (nst == 1 && !reverse)
-        return use_pair(h) ? run_steps_pair(h, n) : use_plane(h) ? run_steps_plane(h, n) : run_steps_axis(h, n);
+        return use_pair(h)                              ? run_steps_pair(h, n)
+               : use_plane(h) || use_plane_regs(h) ? run_steps_plane(h, n)
+                                                        : run_steps_axis(h, n);
     // reverse (dual-state) sweep: X1 | X2 | V, Y1 | Y2, V -- the gradient marginals of each
     // potential factor are taken by the passes on either side of it
     const bool gr = nst == 2;
@@ -887,6 +906,7 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
         return cleanup(HOM4D_EHIP);
     }
     h->plane_built = plane_available(nx, ny);
+    h->regs_built = !h->mixed && cfg->coulomb_mode == HOM4D_COULOMB_TABLE && plane_regs_available(nx, ny);
     h->pair_built = pair_available(nx, ny, h->mixed);
     *out = h;
     return HOM4D_OK;

@@ -160,6 +160,10 @@ struct Plane1Launch {
 bool pair_available(int nx, int ny, bool mixed);
 hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStream_t s);
 
+// The (x2, y2)-plane pass held in registers (plane_regs.hpp), complex128 storage and table form.
+bool plane_regs_available(int nx, int ny);
+hipError_t launch_plane_regs(int nx, int ny, const PassArgs& a, hipStream_t s);
+
 // Reductions and elementwise kernels over all pairs (r1, r2).  The reductions say
 // in *nparts how many partial sums (of their width) they write; at most
 // reduction_parts(nxy, mixed).

@@ -42,6 +42,7 @@ AxisKernel pick_axis3_f64(int axis, int n, int vk, int nst, bool nt, bool pers, 
 AxisKernel pick_axis3_f32(int axis, int n, int vk, int nst, bool nt, bool pers, int w, int* t);
 AxisKernel pick_plane_f64(int nx, int ny, int vk, int* nt);
 AxisKernel pick_plane_f32(int nx, int ny, int vk, int* nt);
+AxisKernel pick_plane_regs(int nx, int ny, bool nt, int* threads, size_t* lds);
 AxisKernel pick_plane1_f64(int nx, int ny, int vk, Plane1Launch* p);
 AxisKernel pick_plane1_f32(int nx, int ny, int vk, Plane1Launch* p);
 
@@ -501,6 +502,27 @@ hipError_t launch_plane1(int nx, int ny, bool mixed, const PassArgs& a, hipStrea
     hipError_t e = allow_lds(fn, p.lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn, dim3((unsigned)(nx * ny / p.w)), dim3(p.threads), p.lds, s, a);
+    return hipGetLastError();
+}
+
+bool plane_regs_available(int nx, int ny) {
+    int threads = 0;
+    size_t lds = 0;
+    return pick_plane_regs(nx, ny, false, &threads, &lds) != nullptr;
+}
+
+hipError_t launch_plane_regs(int nx, int ny, const PassArgs& a, hipStream_t s) {
+    int threads = 0;
+    size_t lds = 0;
+    AxisKernel fn = pick_plane_regs(nx, ny, a.nt != 0, &threads, &lds);
+    if (!fn || a.vdirect || lds > 160 * 1024) return hipErrorInvalidValue;
+    hipError_t e = allow_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    int resident = 0;
+    e = resident_blocks(fn, threads, lds, &resident);
+    if (e != hipSuccess) return e;
+    const int grid = resident > 0 ? std::min(nx * ny, resident) : nx * ny;
+    hipLaunchKernelGGL(fn, dim3((unsigned)grid), dim3(threads), lds, s, a);
     return hipGetLastError();
 }
 
