@@ -14,7 +14,7 @@
 // Dhillon), the reflectors applied to it in reverse, and its sign fixed so that the
 // largest-magnitude component is positive.  Only the lowest pair is wanted, so
 // this takes one reduction where the full Jacobi diagonalisation it replaces took
-// 7-9 sweeps of 3 barriers per rotation step over a matrix in L2: 20.4 -> 0.21 ms
+// 7-9 sweeps of 3 barriers per rotation step over a matrix in L2: 20.4 -> 0.17 ms
 // at nx = 128, ny = 96.
 //
 // k_edge_sum forms psi(x_i, y_j) = sum_m exp(-sigma^2 (k_m - k0)^2)
@@ -88,7 +88,30 @@ __global__ void __launch_bounds__(kThreads) k_edge_state(EdgeArgs g) {
                 M[a][b] = 0.0;
                 if (i < m && j < m) M[a][b] = MEM ? A[(size_t)i * m + j] : element(i, j);
             }
-        eig::tridiag_regs<double, kTR, RA, CB>(M, m - s0, wk, d + s0, keep);
+        if constexpr (CB <= 4) {
+            eig::tridiag_regs<double, kTR, RA, CB>(M, m, m - 1, wk, d, keep);
+        } else {
+            // down to 64 rows, then the form of 64 rows: a step of it moves half the vectors
+            // (m = 96: the kernel 184 -> 172 us)
+            __shared__ double rest[64 * 64];
+            const int n = m - s0 - 64;
+            eig::tridiag_regs<double, kTR, RA, CB, CB / 2>(M, m - s0, n, wk, d + s0, keep);
+#pragma unroll
+            for (int a = 0; a < RA; ++a)
+#pragma unroll
+                for (int b = 0; b < CB; ++b) {
+                    const int i = tr + kTR * a - n, j = tc + 16 * b - n;
+                    if (i >= 0 && j >= 0 && i < 64 && j < 64) rest[i * 64 + j] = M[a][b];
+                }
+            __syncthreads();
+            s0 += n;
+            double L[4][4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) L[a][b] = rest[(tr + kTR * a) * 64 + tc + 16 * b];
+            eig::tridiag_regs<double, kTR, 4, 4>(L, 64, 63, wk, d + s0, keep);
+        }
     }
     __syncthreads();
 
@@ -314,8 +337,9 @@ template <int RA, int CB, bool MEM>
 hipError_t launch_edge_state(const EdgeArgs& e, hipStream_t s) {
     const size_t lds = MEM ? 0 : (size_t)e.ny * (e.ny - 1) / 2 * sizeof(double);
     auto fn = k_edge_state<RA, CB, MEM>;
-    if (lds > 32 * 1024) {
-        // with its static LDS the block is past 64 KB, which has to be allowed
+    if (lds > 8 * 1024) {
+        // with its static LDS (56 KB for more than 64 rows) the block may be past 64 KB,
+        // which has to be allowed
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
         if (err != hipSuccess) return err;

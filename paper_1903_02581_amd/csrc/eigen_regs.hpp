@@ -4,7 +4,9 @@
 // A block of TR x 16 threads holds the matrix with cyclic ownership: thread
 // (tr, tc) keeps elements (tr + TR a, tc + 16 b), so every thread stays busy as the
 // active window shrinks; 512 threads carry 128 x 128 complex values in 128 VGPRs
-// each.  LDS only moves the two vectors of a step.  (The matrix itself does not fit
+// each.  LDS only moves the two vectors of a step, once per wavefront: a lane holds the
+// entries of its number, and a thread's columns of the matrix come from the four rows of its
+// own wavefront by lane swaps.  (The matrix itself does not fit
 // 160 KB of LDS at 128 x 128 complex, and a pass over it in L2 per step is what
 // bounds larger sizes, tridiag_global below.)
 //
@@ -17,14 +19,16 @@
 // itself, from the same LDS values in the same order, so that every thread holds
 // the same bits and takes the same branches.
 //
-// The chain of m - 1 steps on one CU bounds it.  What a step costs beyond its
-// 12 FP64 operations per element is work every wavefront repeats, so there are as few wavefronts
-// as the registers allow, the sums stay in DPP within 16 lanes (a row of the
-// thread grid is one DPP row), and square root and reciprocals are the hardware
-// estimates with two Newton steps.  128 x 128 complex: 278 us (421 us with 1024
-// threads, 32-lane shuffles and library square roots and divisions); 64 x 64: 92
-// us (152); 128 wave numbers' 96 x 96 real matrices, one per CU: 205 us with the
-// eigenvector.
+// The chain of m - 1 steps on one CU bounds it, and in a step the instructions that its one or
+// two wavefronts per SIMD issue.  What a step costs beyond its 12 FP64 operations per element
+// is work every wavefront repeats, so there are as few wavefronts as the registers allow,
+// a large matrix goes on in the form of fewer wavefronts once it has shrunk to 64 rows,
+// the sums stay in DPP and lane swaps, the vectors' entries are kept from the product to the
+// update, and square root and reciprocals are the hardware estimates with two Newton
+// steps.  128 x 128 complex: 239 us (278 us with the columns' entries read from LDS, the
+// reflector's first put in by selects, and one form to the end; 421 us with 1024 threads,
+// 32-lane shuffles and library square roots and divisions); 64 x 64: 75 us (92; 152); 128
+// wave numbers' 96 x 96 real matrices, one per CU: 172 us with the eigenvector (207).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -89,9 +93,34 @@ __device__ __forceinline__ double2 dpp(double2 x) { return make_double2(dpp<CTRL
 __device__ __forceinline__ double add(double a, double b) { return a + b; }
 __device__ __forceinline__ double2 add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
-__device__ __forceinline__ double lane_of(double x, int lane) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
-                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+// The lane swaps between a wavefront's rows of 16 lanes: of x twice, out[0] gets rows
+// (0, 1, 0, 1) and out[1] rows (2, 3, 2, 3) from swap32, rows (0, 0, 2, 2) and
+// (1, 1, 3, 3) from swap16 (all lanes active).
+__device__ __forceinline__ void swap32(double x, double* out) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+    out[0] = __hiloint2double(hi[0], lo[0]);
+    out[1] = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ void swap16(double x, double* out) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(x), false, false);
+    out[0] = __hiloint2double(hi[0], lo[0]);
+    out[1] = __hiloint2double(hi[1], lo[1]);
+}
+// out[r]: x of the lane of row r with the same number within its 16
+__device__ __forceinline__ void rows_of(double x, double* out) {
+    double h[2];
+    swap32(x, h);
+    swap16(h[0], out);
+    swap16(h[1], out + 2);
+}
+__device__ __forceinline__ void rows_of(double2 x, double2* out) {
+    double re[4], im[4];
+    rows_of(x.x, re);
+    rows_of(x.y, im);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[r] = make_double2(re[r], im[r]);
 }
 // Sum over the wavefront, the same in every lane (all lanes active).
 __device__ __forceinline__ double sum64(double x) {
@@ -99,7 +128,10 @@ __device__ __forceinline__ double sum64(double x) {
     x += dpp<kXor7>(x);
     x += dpp<kXor3>(x);
     x += dpp<kXor1>(x);
-    return (lane_of(x, 0) + lane_of(x, 16)) + (lane_of(x, 32) + lane_of(x, 48));
+    double h[2];
+    swap32(x, h);
+    swap16(h[0] + h[1], h);
+    return h[0] + h[1];
 }
 
 // Sums of C values each over 16 lanes, by halves: a stage sends the half of the
@@ -192,78 +224,91 @@ struct Reflector {
         for (int l = 0; l < NL; ++l)
             if (lane + 64 * l == s + 1) mine[l] = v0;
     }
-    // v^H p
-    __device__ __forceinline__ double dot(const T* p) const {
+    // (tau^2 / 2) v^H p; w: w at entries lane + 64 l
+    __device__ __forceinline__ double half_dot(const T* p, T (&w)[NL]) const {
         const int lane = threadIdx.x & 63;
         double g = 0.0;
 #pragma unroll
-        for (int l = 0; l < NL; ++l) g += redot(mine[l], p[lane + 64 * l]);
-        return sum64(g);
+        for (int l = 0; l < NL; ++l) {
+            w[l] = p[lane + 64 * l];
+            g += redot(mine[l], w[l]);
+        }
+        const double half = 0.5 * tau * tau * sum64(g);
+#pragma unroll
+        for (int l = 0; l < NL; ++l) w[l] = msubr(half, mine[l], scaled(w[l], tau));
+        return half;
     }
 };
 
-// Tridiagonalise the m x m matrix of the registers (m <= N = TR RA = 16 CB; elements
-// at and past m zero): d[0 .. m-1] gets the diagonal; step(s, h, x) is called by
-// every thread for each column s = 0 .. m - 2 with its Reflector and the column in
-// LDS (the reflector's entries past s + 1).
-template <class T, int TR, int RA, int CB, class Step>
-__device__ __forceinline__ void tridiag_regs(T (&A)[RA][CB], int m, Work<T>& wk, double* d, Step step) {
+// The first n steps of the tridiagonalisation of the m x m matrix of the registers
+// (n < m <= N = TR RA = 16 CB, n <= 16 CE; elements at and past m zero): step(s, h, x) is
+// called by every thread for each column s = 0 .. n - 1 with its Reflector and the
+// column in LDS (the reflector's entries past s + 1); d[0 .. n-1], and d[n] for n = m - 1,
+// gets the diagonal at the end (from the registers: a store to memory within a step
+// would be waited for at its barriers).  Rows and columns n .. m - 1 then hold what is
+// left to reduce.
+template <class T, int TR, int RA, int CB, int CE = CB, class Step>
+__device__ __forceinline__ void tridiag_regs(T (&A)[RA][CB], int m, int n, Work<T>& wk, double* d, Step step) {
     static_assert(TR * RA == 16 * CB, "a square matrix");
     constexpr int N = TR * RA, NL = (N + 63) / 64;
     const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-    sfor<0, CB>([&](auto cbc) {
+    sfor<0, CE>([&](auto cbc) {
         constexpr int C0 = decltype(cbc)::value, A0 = 16 * C0 / TR;  // first active blocks
-        const int s1 = m < 16 * (C0 + 1) ? m : 16 * (C0 + 1);
+        const int s1 = n < 16 * (C0 + 1) ? n : 16 * (C0 + 1);
         for (int s = 16 * C0; s < s1; ++s) {
             T* x = wk.x[s & 1];
             if (tc == (s & 15)) {
 #pragma unroll
                 for (int a = 0; a < RA; ++a) {
                     const int i = tr + TR * a;
-                    const T v = A[a][C0];
-                    if (i == s) d[s] = real_of(v);
-                    x[i] = i > s ? v : zero_of(v);
+                    x[i] = i > s ? A[a][C0] : zero_of(A[a][C0]);
                 }
             }
             __syncthreads();
-            if (s == m - 1) break;
             const Reflector<T, NL> h(x, s);
             if (h.tau != 0.0) {
+                T vc[4 * NL];  // v at this thread's columns tc + 16 b
+                sfor<C0 / 4, NL>([&](auto lc) { rows_of(h.mine[decltype(lc)::value], vc + 4 * decltype(lc)::value); });
                 {
                     T acc[RA];
 #pragma unroll
                     for (int a = 0; a < RA; ++a) acc[a] = zero_of(h.v0);
 #pragma unroll
-                    for (int b = C0; b < CB; ++b) {
-                        const int j = tc + 16 * b;
-                        const T vj = j == s + 1 ? h.v0 : x[j];
+                    for (int b = C0; b < CB; ++b)
 #pragma unroll
-                        for (int a = A0; a < RA; ++a) acc[a] = madd(A[a][b], vj, acc[a]);
-                    }
+                        for (int a = A0; a < RA; ++a) acc[a] = madd(A[a][b], vc[b], acc[a]);
                     const int row = reduce16<RA>(acc);
                     if ((tc & (16 / RA - 1)) == 0) wk.p[tr + TR * row] = acc[0];
                 }
                 __syncthreads();
-                const double half = 0.5 * h.tau * h.tau * h.dot(wk.p);
-                T vr[RA], wr[RA];
+                T w[NL], vr[RA], wr[RA];
+                const double half = h.half_dot(wk.p, w);
 #pragma unroll
                 for (int a = A0; a < RA; ++a) {
                     const int i = tr + TR * a;
-                    vr[a] = i == s + 1 ? h.v0 : x[i];
+                    vr[a] = x[i];
+                    if (a <= A0 + 1 && i == s + 1) vr[a] = h.v0;
                     wr[a] = msubr(half, vr[a], scaled(wk.p[i], h.tau));
                 }
+                sfor<C0 / 4, NL>([&](auto lc) {
+                    constexpr int l = decltype(lc)::value;
+                    T wj[4];
+                    rows_of(w[l], wj);
 #pragma unroll
-                for (int b = C0; b < CB; ++b) {
-                    const int j = tc + 16 * b;
-                    const T vj = j == s + 1 ? h.v0 : x[j];
-                    const T wj = msubr(half, vj, scaled(wk.p[j], h.tau));
+                    for (int b = 4 * l < C0 ? C0 : 4 * l; b < (4 * l + 4 < CB ? 4 * l + 4 : CB); ++b)
 #pragma unroll
-                    for (int a = A0; a < RA; ++a) A[a][b] = msubc(wr[a], vj, msubc(vr[a], wj, A[a][b]));
-                }
+                        for (int a = A0; a < RA; ++a)
+                            A[a][b] = msubc(wr[a], vc[b], msubc(vr[a], wj[b - 4 * l], A[a][b]));
+                });
             }
             step(s, h, x);
         }
     });
+#pragma unroll
+    for (int a = 0; a < RA; ++a)
+#pragma unroll
+        for (int b = 0; b < CB; ++b)
+            if (tr + TR * a == tc + 16 * b && tr + TR * a < (n == m - 1 ? m : n)) d[tr + TR * a] = real_of(A[a][b]);
 }
 
 // The first n_steps steps on an m x m matrix in global memory (row-major, both
@@ -293,7 +338,8 @@ __device__ __forceinline__ void tridiag_global(T* A, int m, int n_steps, Work<T>
                 if (tc == 0) wk.p[i] = acc;
             }
             __syncthreads();
-            const double half = 0.5 * h.tau * h.tau * h.dot(wk.p);
+            T w[NL];
+            const double half = h.half_dot(wk.p, w);
             for (int i = tr + i0; i < m; i += TR) {
                 const T vr = i == s + 1 ? h.v0 : x[i];
                 const T wr = msubr(half, vr, scaled(wk.p[i], h.tau));

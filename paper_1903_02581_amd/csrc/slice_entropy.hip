@@ -6,7 +6,7 @@
 // Gram matrix, its tridiagonalisation by one workgroup with the matrix in
 // registers (eigen_regs.hpp), the eigenvalues by bisection, a wavefront each, and
 // the sum.  All arithmetic is FP64, sums in a fixed order.  Only (S, norm) leave
-// the GPU.  Measured: 4 + 12 + 278 + 26 + 4 us at m = 128, 4 + 8 + 92 + 14 + 4 us at
+// the GPU.  Measured: 4 + 12 + 239 + 26 + 4 us at m = 128, 4 + 8 + 75 + 14 + 4 us at
 // m = 64, the tridiagonalisation's chain of steps bounding both.  On the host, with the 2m x 2m real embedding and cyclic Jacobi, one call took
 // 15 ms at m = 64 and 0.7-1.0 s at m = 128.
 #include "axis_pass.hpp"
@@ -87,15 +87,16 @@ __global__ void __launch_bounds__(256) k_slice_gram(const double2* a, int m, int
 }
 
 // One block of TR x 16 threads: diagonal d and squared off-diagonals e2 of the
-// tridiagonal form of rho.  With more than eig::kRegMax rows the first steps run
-// on the matrix in memory.
-template <int TR, int RA, int CB>
-__global__ void __launch_bounds__(16 * TR) k_slice_tridiag(double2* rho, int m, double* d, double* e2) {
+// tridiagonal form of rho, steps s0 .. s0 + n - 1 of it; the rest of the matrix goes back to
+// memory if the steps end short of the last.  With more than eig::kRegMax rows the
+// first steps run on the matrix in memory.
+template <int TR, int RA, int CB, int CE = CB>
+__global__ void __launch_bounds__(16 * TR) k_slice_tridiag(double2* rho, int m, int s0, int n, double* d, double* e2) {
     __shared__ eig::Work<double2> wk;
-    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15;
-    int s0 = 0;
+    __shared__ double off[eig::kMax];  // in LDS first: a step's barriers would wait for its store to memory
+    const int tid = threadIdx.x, tr = tid >> 4, tc = tid & 15, first = s0, end = s0 + n;
     auto keep = [&](int s, const auto& h, const double2*) {
-        if (tid == 0) e2[s0 + s] = eig::abs2(h.e);
+        if (tid == 0) off[s0 + s] = eig::abs2(h.e);
     };
     wk.clear();
     if constexpr (TR * RA == eig::kRegMax) {
@@ -113,7 +114,18 @@ __global__ void __launch_bounds__(16 * TR) k_slice_tridiag(double2* rho, int m, 
             const int i = s0 + tr + TR * a, j = s0 + tc + 16 * b;
             A[a][b] = i < m && j < m ? rho[(size_t)i * m + j] : make_double2(0.0, 0.0);
         }
-    eig::tridiag_regs<double2, TR, RA, CB>(A, m - s0, wk, d + s0, keep);
+    eig::tridiag_regs<double2, TR, RA, CB, CE>(A, m - s0, end - s0, wk, d + s0, keep);
+    if constexpr (CE < CB) {
+#pragma unroll
+        for (int a = 0; a < RA; ++a)
+#pragma unroll
+            for (int b = 0; b < CB; ++b) {
+                const int i = s0 + tr + TR * a, j = s0 + tc + 16 * b;
+                if (i >= end && j >= end && i < m && j < m) rho[(size_t)i * m + j] = A[a][b];
+            }
+    }
+    __syncthreads();
+    if (tid >= first && tid < end) e2[tid] = off[tid];
 }
 
 // Eigenvalue k per wavefront.  rho is positive with unit trace, so they lie in
@@ -163,13 +175,18 @@ hipError_t launch_slice_entropy(const void* psi, bool mixed, const SliceIndex& i
                            jy1, jy2, nx, ny, phi, part);
     const int nt = (m + kTile - 1) / kTile;
     hipLaunchKernelGGL(k_slice_gram, dim3(nt, nt), dim3(256), 0, s, phi, m, kd, part, nparts, rho);
-    // the smallest register form that holds the matrix, on as few wavefronts as hold it
+    // the smallest register form that holds the matrix, on as few wavefronts as hold it;
+    // from 128 rows down to 64 in the one, the rest in the other, whose four wavefronts do
+    // a step in 1.2 us where eight take 1.6 (m = 128: 252 -> 239 us)
+    int s0 = 0;
+    if (m > 64) {
+        s0 = m - 64;
+        hipLaunchKernelGGL((k_slice_tridiag<32, 4, 8, 4>), dim3(1), dim3(512), 0, s, rho, m, 0, s0, d, e2);
+    }
     if (m <= 32)
-        hipLaunchKernelGGL((k_slice_tridiag<16, 2, 2>), dim3(1), dim3(256), 0, s, rho, m, d, e2);
-    else if (m <= 64)
-        hipLaunchKernelGGL((k_slice_tridiag<16, 4, 4>), dim3(1), dim3(256), 0, s, rho, m, d, e2);
+        hipLaunchKernelGGL((k_slice_tridiag<16, 2, 2>), dim3(1), dim3(256), 0, s, rho, m, 0, m - 1, d, e2);
     else
-        hipLaunchKernelGGL((k_slice_tridiag<32, 4, 8>), dim3(1), dim3(512), 0, s, rho, m, d, e2);
+        hipLaunchKernelGGL((k_slice_tridiag<16, 4, 4>), dim3(1), dim3(256), 0, s, rho, m, s0, m - 1 - s0, d, e2);
     hipLaunchKernelGGL(k_slice_spectrum, dim3((m + 3) / 4), dim3(256), 0, s, d, e2, m, lam);
     hipLaunchKernelGGL(k_slice_entropy, dim3(1), dim3(256), 0, s, lam, m, part, nparts, out);
     return hipGetLastError();
