@@ -81,14 +81,23 @@ __device__ __forceinline__ void lds_barrier() {
 // 0.717 ms).
 constexpr int potential_batch(int axis, int n, bool c64) { return (c64 && axis == AX_Y2 && n >= 128) ? 2 : 4; }
 
+// Least wavefronts per SIMD the compiler plans for (0: its own choice): the complex64 reverse
+// y1 pass of 128- and 256-point lines is 2 registers past 128, which its LDS would let four
+// wavefronts use (64x128 y1 545 -> 510 us, for 5-10 spills).
+constexpr int axis3_min_waves(int axis, int n, int nst, bool c64) {
+    return c64 && nst == 2 && axis == AX_Y1 && n >= 128 ? 4 : 0;
+}
+
 // WC > 0: the block holds WC lines, a compile-time constant (the nominal width
 // of the pass, axis3_nominal_w), so every LDS address is a per-thread base plus
 // an immediate offset; WC = 0: a.W lines, for grids that allow fewer.
 template <class S, int AXIS, int R1, int R2, int R3, int T, int NST, int VK, bool NT, bool PERS, int WC>
-__global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value)) k_axis3(const PassArgs a) {
+__global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value),
+                                  axis3_min_waves(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value)) k_axis3(const PassArgs a) {
     static_assert(!PERS || NST == 1 || AXIS == AX_X1, "persistent: the forward passes and the reverse x1 pass");
     // the reverse sweep (two states) applies every factor conjugated
     constexpr bool CONJ = NST == 2;
+    constexpr bool SRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 0), LSRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 1);
     using NW = Net3<R1, R2, R3, T>;
     constexpr int N = NW::N, N2 = NW::N2, JA = NW::JA, G1 = NW::G1, G2 = NW::G2, E = NW::E;
     using X = Xchg<S>;
@@ -407,6 +416,11 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
         const uint32_t ntiles = a.ntiles;
         S raw[NST][E];
         auto state = [&](int s) { return reinterpret_cast<S*>(s == 0 ? a.psi : a.lam); };
+        // where the states are read
+        auto from = [&](int s) {
+            if (s == 0 ? SRC : LSRC) return reinterpret_cast<const S*>(s == 0 ? a.src : a.lam_src);
+            return static_cast<const S*>(state(s));
+        };
         double2 kreg = make_double2(0.0, 0.0);  // KROW: entry tid of the next tile's kinetic row
         // the kinetic row of tile tl: y1 of its lines (a tile's lines share y1)
         auto krow_of = [&](uint32_t tl) { return a.ktab + (int64_t)a.dnxy.div(tl * (uint32_t)W) * N; };
@@ -415,7 +429,7 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
             const LineGeom<AXIS> lg(a, tile * (uint32_t)W + (uint32_t)cl);
 #pragma unroll
             for (int s = 0; s < NST; ++s)
-                walk(lg, static_cast<const S*>(state(s)) + lg.base,
+                walk(lg, from(s) + lg.base,
                      [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
             if constexpr (KROW) {
                 if (tid < N) kreg = krow_of(tile)[tid];
@@ -464,7 +478,7 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
                 const LineGeom<AXIS> ln(a, (has_next ? next : tl) * (uint32_t)W + (uint32_t)cl);
                 const S* nbase[NST];
 #pragma unroll
-                for (int s = 0; s < NST; ++s) nbase[s] = state(s) + ln.base;
+                for (int s = 0; s < NST; ++s) nbase[s] = from(s) + ln.base;
                 if constexpr (KROW) {
                     if (has_next && tid < N) kreg = krow_of(next)[tid];
                 }
@@ -493,7 +507,7 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
                     const LineGeom<AXIS> ln(a, next * (uint32_t)W + (uint32_t)cl);
 #pragma unroll
                     for (int s = 0; s < NST; ++s)
-                        walk(ln, static_cast<const S*>(state(s)) + ln.base,
+                        walk(ln, from(s) + ln.base,
                              [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
                     if constexpr (KROW) {
                         if (tid < N) kreg = krow_of(next)[tid];
@@ -519,9 +533,12 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
         S* ps[NST];
         ps[0] = reinterpret_cast<S*>(a.psi) + lg.base;
         if constexpr (NST == 2) ps[1] = reinterpret_cast<S*>(a.lam) + lg.base;
+        const S* from[NST];  // where the states are read
+        from[0] = SRC ? reinterpret_cast<const S*>(a.src) + lg.base : ps[0];
+        if constexpr (NST == 2) from[1] = LSRC ? reinterpret_cast<const S*>(a.lam_src) + lg.base : ps[1];
         S raw[NST][E];
 #pragma unroll
-        for (int s = 0; s < NST; ++s) walk(lg, ps[s], [&](int e, S* p) { raw[s][e] = ld_raw<S, NT>(p); });
+        for (int s = 0; s < NST; ++s) walk(lg, from[s], [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
         after_loads();
 #pragma unroll
         for (int s = 0; s < NST; ++s)

@@ -396,8 +396,13 @@ __global__ void __launch_bounds__(256, axis_min_waves(AXIS, N1 * N2, N1 * N2 / T
     };
 
     S* ps[NST];
+    const S* from[NST];  // where the states are read
     ps[0] = reinterpret_cast<S*>(a.psi) + base;
-    if constexpr (NST == 2) ps[1] = reinterpret_cast<S*>(a.lam) + base;
+    from[0] = axis_reads_apart(AXIS, N, NST, VK, 0) ? reinterpret_cast<const S*>(a.src) + base : ps[0];
+    if constexpr (NST == 2) {
+        ps[1] = reinterpret_cast<S*>(a.lam) + base;
+        from[1] = axis_reads_apart(AXIS, N, NST, VK, 1) ? reinterpret_cast<const S*>(a.lam_src) + base : ps[1];
+    }
 
     {
         S raw[NST][E];
@@ -408,7 +413,7 @@ __global__ void __launch_bounds__(256, axis_min_waves(AXIS, N1 * N2, N1 * N2 / T
             for (int n1 = 0; n1 < N1; ++n1) {
                 const int64_t off = (int64_t)(n1 * N2 + jc) * sN;
 #pragma unroll
-                for (int s = 0; s < NST; ++s) raw[s][jj * N1 + n1] = ld_raw<S, NT>(ps[s] + off);
+                for (int s = 0; s < NST; ++s) raw[s][jj * N1 + n1] = ld_raw<S, NT>(from[s] + off);
             }
         }
         after_loads();

@@ -439,8 +439,8 @@ int run_pass(hom4d* h, int axis, KTab kt, int vmode, int nst, void* lam, bool re
     if (reverse != (nst == 2)) return fail(HOM4D_EINVAL, "internal: a reverse pass carries the adjoint state");
     AxisPlan p = plan_axis(axis, c.nx, c.ny, nst, nst == 2, h->mixed);
     PassArgs a{};
-    a.psi = h->psi;
-    a.lam = lam;
+    a.src = a.psi = h->psi;
+    a.lam_src = a.lam = lam;
     a.nx = c.nx;
     a.ny = c.ny;
     a.dnx = make_div3((uint32_t)c.nx);
@@ -496,7 +496,7 @@ int run_pass(hom4d* h, int axis, KTab kt, int vmode, int nst, void* lam, bool re
 PassArgs plane_args(const hom4d* h, const double2* ktab) {
     const hom4d_cfg& c = h->cfg;
     PassArgs a{};
-    a.psi = h->psi;
+    a.src = a.psi = h->psi;
     a.nx = c.nx;
     a.ny = c.ny;
     a.tw = h->tw_x;

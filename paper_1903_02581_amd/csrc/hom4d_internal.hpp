@@ -31,8 +31,11 @@ struct Div3 {
 // Everything one per-axis pass needs.  Axis lines have length n = nx (x axes)
 // or ny (y axes); the 4D state is row-major [x1][y1][x2][y2].
 struct PassArgs {
-    void* psi;                // state, complex128 or complex64
-    void* lam;                // adjoint state (dual-state passes only)
+    const void* src;          // state to read, complex128 or complex64: psi, or on the passes that
+                              // open or close a run of steps a checkpoint's copy (axis_reads_src)
+    void* psi;                // state to write
+    const void* lam_src;      // adjoint state (dual-state passes only): lam, as src for psi
+    void* lam;
     int nx, ny;
     Div3 dnx, dny, dnxy;      // division by nx, ny and nx ny (line numbers -> coordinates)
     int W;                    // lines per block
@@ -60,6 +63,27 @@ struct PassArgs {
     double kstep;             // 2 pi / Lx
     double y0, ystep;         // y grid
 };
+
+// The passes at whose ends a checkpoint lies: they may read one state and write another,
+// so that the closing pass of a segment leaves its state in the checkpoint and the next segment opens
+// from there, with no copy between.
+__host__ __device__ constexpr bool axis_reads_src(int axis, int nst, int vk) {
+    return vk == 0 && (axis == AX_X1 || (axis == AX_X2 && nst == 1));
+}
+
+// Passes that read a state (0: psi, 1: the adjoint) through a pointer of its own, src or
+// lam_src, also where it is the one they write: the compiler then forms the addresses of the
+// stores anew where it would hold those of the loads over the transform, 16 registers a
+// state for eight elements.  The reverse sweep's passes gain wavefronts by it (complex64 128-point
+// x1 655 -> 573 us at 128x64, x2 548 -> 491, 150 -> 122 registers; 48-point complex128 y1 69
+// -> 64, complex64 96-point y1 198 -> 178), except the two-stage 64-point ones, which
+// lose (complex128 x1 210 -> 230 us, x2 198 -> 208), and y2, whose accesses are one run
+// per line (452 -> 468); of the forward passes the 96-point y1 one (128x96 complex64 0.510 ->
+// 0.475 ms), others within 1%.
+__host__ __device__ constexpr bool axis_reads_apart(int axis, int n, int nst, int vk, int state) {
+    if (state == 0 && axis_reads_src(axis, nst, vk)) return true;
+    return nst == 1 ? axis == AX_Y1 && n == 96 : axis != AX_Y2 && n != 64;
+}
 
 struct FftShape {
     int n1, n2, t;  // n = n1 * n2, t threads per line
