@@ -432,14 +432,19 @@ struct GradCtx {
     double* m_y2;
 };
 
+// src: the state read, dst: the state written (null: the bound one); another than the
+// bound one on the passes that open or close a segment only (axis_reads_src).
 int run_pass(hom4d* h, int axis, KTab kt, int vmode, int nst, void* lam, bool reverse, int gflags,
-             const GradCtx* g) {
+             const GradCtx* g, const void* src = nullptr, void* dst = nullptr) {
     const hom4d_cfg& c = h->cfg;
     // the pass kernels conjugate every factor exactly when they carry two states
     if (reverse != (nst == 2)) return fail(HOM4D_EINVAL, "internal: a reverse pass carries the adjoint state");
+    if ((src || dst) && !axis_reads_src(axis, nst, vmode))
+        return fail(HOM4D_EINVAL, "internal: this pass works in place");
     AxisPlan p = plan_axis(axis, c.nx, c.ny, nst, nst == 2, h->mixed);
     PassArgs a{};
-    a.src = a.psi = h->psi;
+    a.src = src ? src : h->psi;
+    a.psi = dst ? dst : h->psi;
     a.lam_src = a.lam = lam;
     a.nx = c.nx;
     a.ny = c.ny;
@@ -556,14 +561,14 @@ bool use_pair(const hom4d* h) {
 
 // n whole forward steps in two passes per step:
 //   X1 | [X2, V, Y2] | [Y1, V, X1]  ...  closing X2 half.
-int run_steps_pair(hom4d* h, int64_t n) {
+int run_steps_pair(hom4d* h, int64_t n, const void* src, void* dst) {
     int rc;
-    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr))) return rc;
+    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr, src))) return rc;
     for (int64_t i = 0; i < n; ++i) {
         if ((rc = run_plane(h, i == 0 ? KX_HALF : KX_FULL))) return rc;
         if ((rc = run_plane1(h, i == n - 1 ? KX_HALF : KX_FULL))) return rc;
     }
-    return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr);
+    return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr, nullptr, dst);
 }
 
 // Steps in three passes around the register-held plane pass, with the same exceptions.
@@ -573,9 +578,9 @@ bool use_plane_regs(const hom4d* h) {
 
 // n whole forward steps in three passes per step:
 //   X1 | [X2, V, Y2] (plane) | [Y1, V]  ...  closing X1, X2 halves.
-int run_steps_plane(hom4d* h, int64_t n) {
+int run_steps_plane(hom4d* h, int64_t n, const void* src, void* dst) {
     int rc;
-    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr))) return rc;
+    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr, src))) return rc;
     for (int64_t i = 0; i < n; ++i) {
         const bool last = i == n - 1;
         const KTab kx = i == 0 ? KX_HALF : KX_FULL;
@@ -583,14 +588,14 @@ int run_steps_plane(hom4d* h, int64_t n) {
         if ((rc = run_pass(h, AX_Y1, KY_FULL, 2, 1, nullptr, false, 0, nullptr))) return rc;
         if ((rc = run_pass(h, AX_X1, last ? KX_HALF : KX_FULL, 0, 1, nullptr, false, 0, nullptr))) return rc;
     }
-    return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr);
+    return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr, nullptr, dst);
 }
 
 // n whole forward steps in four per-axis passes, the potential factor as the
 // epilogue of the x2 and y2 passes:  X1 | X2, V | Y1 | Y2, V | X1 ...
-int run_steps_axis(hom4d* h, int64_t n) {
+int run_steps_axis(hom4d* h, int64_t n, const void* src, void* dst) {
     int rc;
-    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr))) return rc;
+    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, 1, nullptr, false, 0, nullptr, src))) return rc;
     if ((rc = run_pass(h, AX_X2, KX_HALF, 2, 1, nullptr, false, 0, nullptr))) return rc;
     for (int64_t i = 0; i < n; ++i) {
         const bool last = i == n - 1;
@@ -598,23 +603,26 @@ int run_steps_axis(hom4d* h, int64_t n) {
         if ((rc = run_pass(h, AX_Y2, KY_FULL, 2, 1, nullptr, false, 0, nullptr))) return rc;
         const KTab kx = last ? KX_HALF : KX_FULL;
         if ((rc = run_pass(h, AX_X1, kx, 0, 1, nullptr, false, 0, nullptr))) return rc;
-        if ((rc = run_pass(h, AX_X2, kx, last ? 0 : 2, 1, nullptr, false, 0, nullptr))) return rc;
+        if ((rc = run_pass(h, AX_X2, kx, last ? 0 : 2, 1, nullptr, false, 0, nullptr, nullptr, last ? dst : nullptr)))
+            return rc;
     }
     return HOM4D_OK;
 }
 
-// n whole steps with merged X halves; the state is closed at the end.
-int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradCtx* g) {
+// n whole steps with merged X halves; the state is closed at the end.  They start from src
+// and (forward) leave their result in dst (null: the bound state; it is overwritten in any case).
+int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradCtx* g, const void* src = nullptr,
+              void* dst = nullptr) {
     if (n <= 0) return HOM4D_OK;
     if (nst == 1 && !reverse)
-        return use_pair(h)                              ? run_steps_pair(h, n)
-               : use_plane(h) || use_plane_regs(h) ? run_steps_plane(h, n)
-                                                        : run_steps_axis(h, n);
+        return use_pair(h)                              ? run_steps_pair(h, n, src, dst)
+               : use_plane(h) || use_plane_regs(h) ? run_steps_plane(h, n, src, dst)
+                                                        : run_steps_axis(h, n, src, dst);
     // reverse (dual-state) sweep: X1 | X2 | V, Y1 | Y2, V -- the gradient marginals of each
     // potential factor are taken by the passes on either side of it
     const bool gr = nst == 2;
     int rc;
-    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, nst, lam, reverse, gr ? G_GB : 0, g))) return rc;
+    if ((rc = run_pass(h, AX_X1, KX_HALF, 0, nst, lam, reverse, gr ? G_GB : 0, g, src))) return rc;
     if ((rc = run_pass(h, AX_X2, KX_HALF, 0, nst, lam, reverse, gr ? (G_GB | G_MOUT) : 0, g))) return rc;
     for (int64_t i = 0; i < n; ++i) {
         const bool last = i == n - 1;
@@ -628,8 +636,9 @@ int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradC
     return HOM4D_OK;
 }
 
-
-
+// Whether the passes can read and write checkpoints in the pool; copies serve one that is
+// off their 16-byte accesses.
+bool pool_in_passes(const hom4d* h) { return (uintptr_t)h->pool % 16 == 0; }
 
 // Sums of nparts partial sums of the given width; they go straight to pinned host memory.
 int fetch_reduction(hom4d* h, int nparts, int width, double* out) {
@@ -810,16 +819,19 @@ int grad_sweep(hom4d* h, const double* w_top, const double* coeffs, void* d_lamb
     HIP_TRY(launch_loss_lambda(h->psi, d_lambda, h->mixed, h->w_dev, coeffs, h->nxy, h->red_part, &nparts, h->stream));
     double L = 0.0;
     if ((rc = fetch_reduction(h, nparts, 1, &L))) return rc;
-    // reverse sweep, segment by segment, restoring the state at every checkpoint
+    // reverse sweep, segment by segment, each from the checkpoint at its end (the last
+    // partial one from the state as it is); the first checkpoint is the state it leaves
+    const void* from = nullptr;
     int64_t seg_end = h->rec_steps;
     for (int64_t k = h->rec_steps / h->ckpt_every; k >= 0; --k) {
         const int64_t seg_start = k * h->ckpt_every;
-        if (seg_end > seg_start) {
-            if ((rc = run_steps(h, seg_end - seg_start, 2, d_lambda, true, &g))) return rc;
-        }
-        HIP_TRY(hipMemcpyAsync(h->psi, h->pool + (size_t)k * h->state_bytes, h->state_bytes, hipMemcpyDeviceToDevice,
-                               h->stream));
+        if ((rc = run_steps(h, seg_end - seg_start, 2, d_lambda, true, &g, from))) return rc;
+        char* slot = h->pool + (size_t)k * h->state_bytes;
         seg_end = seg_start;
+        from = slot;
+        if (k > 0 && pool_in_passes(h)) continue;
+        HIP_TRY(hipMemcpyAsync(h->psi, slot, h->state_bytes, hipMemcpyDeviceToDevice, h->stream));
+        from = nullptr;
     }
     HIP_TRY(launch_grad_finish(g.m_x2, (int)(c.ny / l.w_x2), g.m_y2, (int)(c.nx / l.w_y2), g.m_y1, g.m_x1, c.nx,
                                c.ny, c.dt_fs / h->u.hbar, dldv_dev, h->stream));
@@ -1128,13 +1140,18 @@ int hom4d_step(hom4d* h, int64_t n) {
     if (n > INT64_MAX - h->rec_steps || (h->rec_steps + n) / h->ckpt_every >= slots)
         return fail(HOM4D_ENOMEM, "the checkpoints of %lld more recorded steps do not fit the pool (%zu bytes)",
                     (long long)n, h->pool_bytes);
-    // close the state on every checkpoint boundary and copy it out; a failure
+    // close the state on every checkpoint boundary: in the checkpoint itself, which the
+    // next segment starts from (a copy took 204 us at 128x64 complex64, a pass takes 230-300), and
+    // at the end of the call in the bound state, with a copy to the checkpoint; a failure
     // part way closes the recording (its checkpoints no longer match the state)
+    const void* from = nullptr;
     int64_t left = n;
     while (left > 0) {
         const int64_t to_ck = h->ckpt_every - (h->rec_steps % h->ckpt_every);
         const int64_t m = std::min(left, to_ck);
-        int rc = run_steps(h, m, 1, nullptr, false, nullptr);
+        char* slot = m == to_ck ? h->pool + (size_t)((h->rec_steps + m) / h->ckpt_every) * h->state_bytes : nullptr;
+        char* dst = m < left && pool_in_passes(h) ? slot : nullptr;
+        int rc = run_steps(h, m, 1, nullptr, false, nullptr, from, dst);
         if (rc) {
             h->rec = false;
             return rc;
@@ -1142,10 +1159,9 @@ int hom4d_step(hom4d* h, int64_t n) {
         h->rec_steps += m;
         h->step += m;
         left -= m;
-        if (h->rec_steps % h->ckpt_every == 0) {
-            const size_t slot = (size_t)(h->rec_steps / h->ckpt_every);
-            const hipError_t e = hipMemcpyAsync(h->pool + slot * h->state_bytes, h->psi, h->state_bytes,
-                                                hipMemcpyDeviceToDevice, h->stream);
+        from = dst;
+        if (slot && !dst) {
+            const hipError_t e = hipMemcpyAsync(slot, h->psi, h->state_bytes, hipMemcpyDeviceToDevice, h->stream);
             if (e != hipSuccess) {
                 h->rec = false;
                 return fail(HOM4D_EHIP, "checkpoint copy: %s", hipGetErrorString(e));
