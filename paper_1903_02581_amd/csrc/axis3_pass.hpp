@@ -19,25 +19,22 @@
 // stages the line is exchanged through LDS, each stage reading and writing its
 // own disjoint set of positions.
 //
-// PERS (the forward one-state passes and the reverse sweep's x1 pass): the
-// kernel is persistent: a block
-// walks tiles of W lines (tile = blockIdx.x, + gridDim.x, ...) and issues the
-// loads of its next tile while it transforms the current one (at its start, or
-// on the wide forms in four parts between its exchanges), so that the HBM
-// reads of one tile overlap the arithmetic and LDS exchanges of the previous
-// one inside the block, instead of relying on other resident blocks being out
-// of phase.  The two-state form loads and stores both states and takes its
-// gradient partial sums per tile, with LDS-only barriers, and synchronises once
-// more after them before the next tile reuses the exchange area.  Its exchanges synchronise the block on LDS alone (lds_barrier),
-// leaving the prefetch loads and the stores in flight.  It pays where a pass
-// has few resident blocks per CU: measured on the complex64 x1 and y1 passes
-// of the 256x128 state (x1 6.07 -> 5.36 ms, y1 4.46 -> 4.20 ms); the x2 and
-// y2 passes, the FP64 passes and n = 96 lines ran slower that way (128x96
-// complex64 y1 0.52 -> 0.61 ms, y2 0.72 -> 0.86 ms; 128x128 FP64 x1 1.62 ->
-// 1.79 ms), so they keep one tile per block.  No global load is waited for
-// inside a tile's transform (the x1 pass takes its kinetic factors from LDS),
-// and the first tile is peeled off the loop, so that the only wait for the
-// prefetch, at the start of the next tile, leaves the stores in flight.
+// PERS (the forward complex64 x1 pass of 128- and 256-point lines): the kernel is
+// persistent: a block walks tiles of W lines (tile = blockIdx.x, + gridDim.x, ...) and
+// issues the loads of its next tile while it transforms the current one (on the nominal
+// width in four parts, from its start and between its exchanges), so that the HBM reads of
+// one tile overlap the arithmetic and LDS exchanges of the previous one inside the block,
+// instead of relying on other resident blocks being out of phase.  Its exchanges
+// synchronise the block on LDS alone (lds_barrier), leaving the prefetch loads and the
+// stores in flight.  It pays where a pass has few resident blocks per CU: the 256-point x1
+// pass, one 1024-thread block per CU, 5.87 ms without and 4.45 ms with it at 256x128; 128x64
+// x1 237 and 228 us.  The y1 passes, and the reverse x1 pass with its two states, have
+// enough wavefronts once they hold no addresses over the transform (axis_reads_apart):
+// 256x128 y1 3.64 ms persistent, 3.25 so, 48x256 y1 590 and 530 us, reverse x1 12.1 and
+// 11.0 ms at 256x128.  FP64 and n = 96 lines ran slower persistent as well (128x128 FP64 x1
+// 1.62 -> 1.79 ms).  No global load is waited for inside a tile's transform (the kinetic
+// factors come from LDS), and the first tile is peeled off the loop, so that the only wait
+// for the prefetch, at the start of the next tile, leaves the stores in flight.
 //
 // The arithmetic is FP64 for both storage types.  With complex64 storage the
 // exchange area holds complex64 too: each exchange then rounds like one more
@@ -94,7 +91,7 @@ constexpr int axis3_min_waves(int axis, int n, int nst, bool c64) {
 template <class S, int AXIS, int R1, int R2, int R3, int T, int NST, int VK, bool NT, bool PERS, int WC>
 __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value),
                                   axis3_min_waves(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value)) k_axis3(const PassArgs a) {
-    static_assert(!PERS || NST == 1 || AXIS == AX_X1, "persistent: the forward passes and the reverse x1 pass");
+    static_assert(!PERS || (NST == 1 && AXIS == AX_X1 && VK == 0), "persistent: the forward x1 pass");
     // the reverse sweep (two states) applies every factor conjugated
     constexpr bool CONJ = NST == 2;
     constexpr bool SRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 0), LSRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 1);
@@ -116,12 +113,12 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
 
     // twiddles w_n^j (and, on y axes, the kinetic factor) staged after the exchange area
     constexpr bool KT_LDS = (AXIS == AX_Y1 || AXIS == AX_Y2);
-    // persistent x1 pass: the tile's kinetic row (its lines share y1) comes from
+    // persistent: the tile's kinetic row (its lines share y1) comes from
     // one of two LDS rows after the twiddles, written at the start of the tile
     // from a register loaded with the previous tile's prefetch, so that no
     // global load is issued inside the transform (a wait for one would also wait
     // for the next tile's loads and the previous tile's stores, issued earlier)
-    constexpr bool KROW = PERS && AXIS == AX_X1;
+    constexpr bool KROW = PERS;
     const double2* krow = nullptr;
     const int LS = W + 1;  // padded LDS row: one line position across the block's W lines
     typename X::T* lds = reinterpret_cast<typename X::T*>(lds_raw);
@@ -362,37 +359,15 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
             // marginal per line on the x1 and y1 axes (the line's threads summed in
             // fixed order), per block on x2 and y2 (a block's lines share r1)
             double* red = reinterpret_cast<double*>(lds_raw);
-            // block-wide synchronisation on LDS alone in the persistent form (the
-            // next tile's loads stay in flight)
-            auto bsync = [&]() {
-                if constexpr (PERS)
-                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-                else
-                    __syncthreads();
-            };
             if (a.gflags & G_GB) {
-                double sum;
-                if constexpr (PERS) {
-                    // block_sum's order: the wavefront's butterfly, then the wavefronts in turn
-                    double g = gb_acc;
-#pragma unroll
-                    for (int o = 32; o >= 1; o >>= 1) g += __shfl_xor(g, o, 64);
-                    bsync();
-                    if ((tid & 63) == 0) red[tid >> 6] = g;
-                    bsync();
-                    sum = 0.0;
-                    if (tid == 0)
-                        for (int w = 0; w < (T * W) / 64; ++w) sum += red[w];
-                } else {
-                    sum = block_sum(gb_acc, red);
-                }
+                const double sum = block_sum(gb_acc, red);
                 if (tid == 0) a.gb_part[blk] += sum;
             }
             if (a.gflags & (G_MIN | G_MOUT)) {
                 if constexpr (AXIS == AX_X1 || AXIS == AX_Y1) {
-                    bsync();
+                    __syncthreads();
                     red[t * W + cl] = gm_acc;
-                    bsync();
+                    __syncthreads();
                     if (t == 0) {
                         double sum = 0.0;
                         for (int q = 0; q < T; ++q) sum += red[q * W + cl];
@@ -402,10 +377,6 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
                     const double sum = block_sum(gm_acc, red);
                     if (tid == 0) a.marg_part[blk] += sum;
                 }
-            }
-            // the next tile's first exchange reuses the area the sums were read from
-            if constexpr (PERS) {
-                if (a.gflags & (G_GB | G_MIN | G_MOUT)) bsync();
             }
         }
     };
@@ -436,24 +407,18 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
             }
         }
         uint32_t it = 0;  // the block's tile count: parity selects the kinetic row
-        // The wide persistent forms -- the 256-point x1 pass (1024-thread blocks,
-        // one per CU whatever their registers up to 128) and the 128-point x1 and
-        // y1 passes (32-line 512-thread blocks, two per CU at up to 128 registers) -- keep
-        // the thread's tile-invariant addresses in registers, and issue the next
-        // tile's loads in parts while the current tile is transformed, instead of
-        // all at its start (the schedule below).  Elsewhere the thread's line slot and
-        // position index pass through an empty asm each tile, so that the LDS and
-        // table addresses derived from them are recomputed per tile rather than
-        // hoisted out of the loop and held in registers for all of it, and the
-        // loads go out at once.  Hoisting: 256x128 x1 96 -> 120 VGPRs, about 8
-        // fewer VALU instructions per point, 5.25 -> 5.12 ms; y1 with 32-line
-        // blocks 4.28 -> 3.89 ms.  Spreading (the schedule below), 256x128: x1
-        // 5.10 -> 4.41 ms, y1 3.83 -> 3.57-3.62 ms, with fewer registers held over
-        // the tile; the 128-point x1 pass in 32-line blocks, hoisted and in four
-        // parts from the start: 128x96 0.559 -> 0.526 ms, 128x64 0.279 -> 0.234 ms
-        // (its 16-line blocks measured 0.549 -> 0.554 ms in four parts and
-        // loads at once).
-        constexpr bool WIDE = WC > 0 && ((AXIS == AX_X1 && (N == 256 || N == 128)) || (AXIS == AX_Y1 && N == 128));
+        // At the nominal width -- 1024-thread blocks, one per CU whatever their registers up to 128, at
+        // 256 points, 32-line 512-thread blocks, two per CU at up to 128 registers, at 128 --
+        // the thread's tile-invariant addresses stay in registers, and the next tile's loads
+        // are issued in parts while the current tile is transformed, instead of all at its
+        // start (the schedule below).  At other widths the thread's line slot and position
+        // index pass through an empty asm each tile, so that the LDS and table addresses derived from
+        // them are recomputed per tile rather than hoisted out of the loop and held in
+        // registers for all of it, and the loads go out at once.  256x128 x1: hoisting 5.25 ->
+        // 5.12 ms (about 8 fewer VALU instructions per point), spreading 5.10 -> 4.41 ms,
+        // with fewer registers held over the tile; the 128-point pass, hoisted and spread:
+        // 128x96 0.559 -> 0.526 ms, 128x64 0.279 -> 0.234 ms.
+        constexpr bool WIDE = WC > 0;
         auto one_tile = [&](uint32_t tl) {
             if constexpr (!WIDE) asm volatile("" : "+v"(t), "+v"(cl));
             const uint32_t line = tl * (uint32_t)W + (uint32_t)cl;
@@ -482,17 +447,14 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
                 if constexpr (KROW) {
                     if (has_next && tid < N) kreg = krow_of(next)[tid];
                 }
-                // NP parts of the E elements, part j issued at slot FIRST + j (slot -1:
-                // before the first stage, slot k >= 0: after exchange k): x1 in four
-                // parts from the start of the tile, y1 in two after its first two
-                // exchanges, the fastest of the schedules measured (x1 four parts
-                // after the four exchanges 4.56-4.65 ms, three or two from the start
-                // 4.62 and 4.76 ms; y1 four parts 3.59-3.68 ms)
-                constexpr int NP = AXIS == AX_X1 ? 4 : 2;
-                constexpr int FIRST = AXIS == AX_X1 ? -1 : 0;
+                // NP parts of the E elements, part j issued at slot j - 1 (slot -1: before the first
+                // stage, slot k >= 0: after exchange k), the fastest of the schedules measured
+                // (after the four exchanges 4.56-4.65 ms at 256x128, three or two parts from the
+                // start 4.62 and 4.76 ms)
+                constexpr int NP = 4;
                 constexpr int PART = (E + NP - 1) / NP;
                 auto part = [&](int slot) {
-                    const int j = slot - FIRST;
+                    const int j = slot + 1;
                     if (has_next && j >= 0 && j < NP) {
 #pragma unroll
                         for (int s = 0; s < NST; ++s)
@@ -560,23 +522,29 @@ AxisKernel pick_w(int w) {
 template <class S, int AXIS, int NST, int VK, bool NT, bool PERS = false>
 AxisKernel pick3(int n, int w, int* t) {
     switch (n) {
-        case 96: *t = 8; return pick_w<S, AXIS, 12, 4, 2, 8, NST, VK, NT, PERS>(w);
+        case 96:
+            if constexpr (!PERS) {
+                *t = 8;
+                return pick_w<S, AXIS, 12, 4, 2, 8, NST, VK, NT, PERS>(w);
+            }
+            break;
         case 128: *t = 16; return pick_w<S, AXIS, 8, 4, 4, 16, NST, VK, NT, PERS>(w);
         case 256: *t = 32; return pick_w<S, AXIS, 8, 8, 4, 32, NST, VK, NT, PERS>(w);
-        default: *t = 0; return nullptr;
+        default: break;
     }
+    *t = 0;
+    return nullptr;
 }
 
 // Forward single-state passes: the x1 pass carries no potential factor, the
 // y2 pass always carries it, x2 and y1 either.  Reverse dual-state passes: the
 // x passes carry none, y1 (before its transform) and y2 (after) carry it.
-// Persistent forms: the x1 and y1 passes without a potential factor.
+// Persistent form: the complex64 x1 pass of 128- and 256-point lines.
 template <class S, bool NT>
 AxisKernel pick_axis3_nt(int axis, int n, int vk, int nst, bool pers, int w, int* t) {
     if (pers) {
-        if (nst == 1 && vk == 0 && axis == AX_X1) return pick3<S, AX_X1, 1, 0, NT, true>(n, w, t);
-        if (nst == 1 && vk == 0 && axis == AX_Y1) return pick3<S, AX_Y1, 1, 0, NT, true>(n, w, t);
-        if (nst == 2 && vk == 0 && axis == AX_X1) return pick3<S, AX_X1, 2, 0, NT, true>(n, w, t);
+        if constexpr (!std::is_same<S, double2>::value)
+            if (nst == 1 && vk == 0 && axis == AX_X1) return pick3<S, AX_X1, 1, 0, NT, true>(n, w, t);
         *t = 0;
         return nullptr;
     }

@@ -153,25 +153,20 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         // The complex64 x2 pass at n = 128 takes 32 lines as well (512 threads,
         // complex64 entries within 80 KB): x2+V 842 -> 812 us at 128 x 96, 317 ->
         // 310 us at 128 x 64 (the one-tile x1 pass measured slower that way, 581
-        // -> 647); so do the persistent y1 and x1 passes, with their addresses
-        // kept in registers and the next tile's loads issued in parts (256 x 128
-        // y1: 4.28 -> 3.83 ms; 128 x 96 x1: 0.559 -> 0.526 ms).
+        // -> 647); so do the y1 pass and the persistent x1 pass, with its
+        // addresses kept in registers and the next tile's loads issued in parts (128 x 96
+        // x1: 0.559 -> 0.526 ms).
         int64_t w = axis3_nominal_w(axis, p.n, t3, nst, mixed);
         w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
         if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad));
         if (axis == AX_Y2 && grad) w = std::min<int64_t>(w, ilog2_pow2_divisor(nx));
         p.W = (int)std::max<int64_t>(w, 1);
-        // persistent form on the complex64 x1 and y1 passes of 128- and 256-point
-        // lines (256x128: x1 6.07 -> 5.36 ms, y1 4.46 -> 4.20 ms); the other
-        // passes, FP64 and 96-point lines measured slower that way.  The x1 form
-        // stages each tile's kinetic row, so a tile's lines share y1 and the
-        // block's threads cover a row.
-        // The reverse sweep's two-state x1 pass of 256-point lines (one 512-thread
-        // block per CU at its 143 registers, so none out of phase to hide its
-        // loads) takes the persistent form too: 256 x 128 reverse sweep 0.946 ->
-        // 0.880 s over 20 recorded steps, gradients unchanged to rounding.
-        p.pers = mixed && p.n >= 128 && (axis == AX_X1 || axis == AX_Y1) && (nst == 1 || (axis == AX_X1 && p.n == 256));
-        if (p.pers && axis == AX_X1 && (nxy % p.W != 0 || (int64_t)p.t * p.W < p.n)) p.pers = false;
+        // persistent form on the complex64 x1 pass of 128- and 256-point lines (256x128 x1
+        // 5.87 ms without, 4.45 ms with it); the other passes, the reverse x1 pass, FP64 and
+        // 96-point lines measured slower that way.  It stages each tile's kinetic row, so a
+        // tile's lines share y1 and the block's threads cover a row.
+        p.pers = mixed && p.n >= 128 && axis == AX_X1 && nst == 1;
+        if (p.pers && (nxy % p.W != 0 || (int64_t)p.t * p.W < p.n)) p.pers = false;
         p.lds = axis3_pass_lds_bytes(axis, p.n, p.W, nst, mixed, p.pers);
         return p;
     }

@@ -78,11 +78,12 @@ __host__ __device__ constexpr bool axis_reads_src(int axis, int nst, int vk) {
 // x1 655 -> 573 us at 128x64, x2 548 -> 491, 150 -> 122 registers; 48-point complex128 y1 69
 // -> 64, complex64 96-point y1 198 -> 178), except the two-stage 64-point ones, which
 // lose (complex128 x1 210 -> 230 us, x2 198 -> 208), and y2, whose accesses are one run
-// per line (452 -> 468); of the forward passes the 96-point y1 one (128x96 complex64 0.510 ->
-// 0.475 ms), others within 1%.
+// per line (452 -> 468); of the forward passes the three-stage y1 one (128x96 complex64 0.510 ->
+// 0.475 ms, 256x128 3.37 -> 3.25, 48x256 590 -> 530 us), others within 1% or slower (x2+V
+// 0.675 -> 0.691 ms at 128x96).
 __host__ __device__ constexpr bool axis_reads_apart(int axis, int n, int nst, int vk, int state) {
     if (state == 0 && axis_reads_src(axis, nst, vk)) return true;
-    return nst == 1 ? axis == AX_Y1 && n == 96 : axis != AX_Y2 && n != 64;
+    return nst == 1 ? axis == AX_Y1 && n >= 96 : axis != AX_Y2 && n != 64;
 }
 
 struct FftShape {
@@ -116,7 +117,7 @@ __host__ __device__ constexpr int axis3_block_threads(int axis, int n, int nst, 
 __host__ __device__ constexpr int axis3_nominal_w(int axis, int n, int t3, int nst, bool mixed) {
     const int bt = axis3_block_threads(axis, n, nst, mixed);
     const bool wide = n != 128;
-    // the complex64 x2 and (persistent) x1 and y1 passes of 128-point lines: 32 lines
+    // the complex64 x2, (persistent) x1 and y1 passes of 128-point lines: 32 lines
     const bool c64_32 = n == 128 && nst == 1 && mixed && (axis == AX_X2 || axis == AX_Y1 || axis == AX_X1);
     int w = (bt == 1024 ? 1024 : (wide || c64_32) ? 512 : 256) / t3;
     const int cap = (bt == 1024 || c64_32) ? (81920 - 2 * n * 16) / (n * 8) - 1
@@ -158,11 +159,11 @@ __host__ __device__ constexpr size_t axis3_lds_bytes(int n, int w, int nst, bool
 // ... of a pass: the persistent x1 pass keeps two kinetic rows after its
 // twiddles, one more row of n complex128 entries
 __host__ __device__ constexpr size_t axis3_pass_lds_bytes(int axis, int n, int w, int nst, bool c64, bool pers) {
-    return axis3_lds_bytes(n, w, nst, c64) + ((pers && axis == AX_X1) ? (size_t)n * 16u : 0u);
+    return axis3_lds_bytes(n, w, nst, c64) + (pers ? (size_t)n * 16u : 0u);
 }
 
 // Launch one per-axis pass: blocks of t*W threads, nlines/W blocks; with pers
-// (three-stage forward x1 and y1 passes only) the persistent form, as many
+// (three-stage forward complex64 x1 pass only) the persistent form, as many
 // blocks as fit the device at once, walking the a.ntiles = nlines/W tiles.
 hipError_t launch_axis(int axis, int n, bool mixed, int nst, bool pers, const PassArgs& a, int64_t nlines,
                        size_t lds_bytes, hipStream_t s);
