@@ -288,11 +288,12 @@ int hom4d_grad_end(hom4d* h);
  * with V fused.  plan = 1: four per-axis passes (x1; x2 then V; y1; y2 then V).
  * Both apply the same factors in the same order (Sec. II.C Eq. (evoloperat)).
  * The reverse (adjoint) sweep always uses the per-axis passes.  On small grids
- * (nx ny <= 1024) a plan-0 step runs as two fused kernels, X2 V Y2 and Y1 V X1, except in
- * recorded complex64 runs and while pass timing is on, and on complex128 128x128, 128x64 and
- * 64x128 grids with the Coulomb table X2, V and Y2 run as one pass with the plane
- * in registers, except while pass timing is on; hom4d_pass_plan and the
- * pass kinds of hom4d_pass_times keep naming the plan above.
+ * (nx ny <= 1024, lengths 8 to 64 but 64x12) a plan-0 step runs as two fused
+ * kernels, X2 V Y2 and Y1 V X1, except in recorded complex64 runs and while pass
+ * timing is on, and on complex128 128x128, 128x64 and 64x128 grids with the
+ * Coulomb table X2, V and Y2 run as one pass with the plane in registers, except
+ * while pass timing is on; hom4d_pass_plan and the pass kinds of
+ * hom4d_pass_times keep naming the plan above.
  * hom4d_pass_plan returns the number of passes per step in use (3 or 4). */
 int hom4d_set_pass_plan(hom4d* h, int32_t plan);
 int hom4d_pass_plan(hom4d* h);
