@@ -84,8 +84,8 @@ __device__ __forceinline__ void st16(S* p, const double2* v) {
         *reinterpret_cast<float4*>(p) = make_float4((float)v[0].x, (float)v[0].y, (float)v[1].x, (float)v[1].y);
 }
 
-// The r2 positions of a thread: K groups of kVec<S> consecutive ones (nxy is a
-// multiple of 16, so a group is inside the row or outside it).
+// The r2 positions of a thread: K groups of kVec<S> consecutive ones (every supported nxy is a
+// multiple of 4, so a group is inside the row or outside it).
 template <class S, int K>
 struct PairTile {
     int pos[K];
@@ -343,17 +343,19 @@ __global__ void __launch_bounds__(256) k_grad_finish(const double* m_x2, int bpr
                                                      const double* m_y1, const double* m_x1, int nx, int ny,
                                                      double gscale, double* dldv) {
     __shared__ double sum[16][kFinishEntries + 1];
-    const int nxy = nx * ny;  // a multiple of 16
+    const int nxy = nx * ny;
     const int c = threadIdx.x % kFinishEntries, t = threadIdx.x / kFinishEntries;
     const int r = blockIdx.x * kFinishEntries + c;
     double g = 0.0;
-    for (int q = t; q < bpr_x2; q += 16) g += m_x2[(int64_t)r * bpr_x2 + q];
-    for (int q = t; q < bpr_y2; q += 16) g += m_y2[(int64_t)r * bpr_y2 + q];
-    for (int i = t; i < nx; i += 16) g += m_y1[(int64_t)i * nxy + r];
-    for (int j = t; j < ny; j += 16) g += m_x1[(int64_t)j * nxy + r];
+    if (r < nxy) {  // the last block is partial on grids of 4 and 6 by 6 and 12 points
+        for (int q = t; q < bpr_x2; q += 16) g += m_x2[(int64_t)r * bpr_x2 + q];
+        for (int q = t; q < bpr_y2; q += 16) g += m_y2[(int64_t)r * bpr_y2 + q];
+        for (int i = t; i < nx; i += 16) g += m_y1[(int64_t)i * nxy + r];
+        for (int j = t; j < ny; j += 16) g += m_x1[(int64_t)j * nxy + r];
+    }
     sum[t][c] = g;
     __syncthreads();
-    if (t == 0) {
+    if (t == 0 && r < nxy) {
         double a = 0.0;
         for (int q = 0; q < 16; ++q) a += sum[q][c];
         dldv[r] = gscale * a;
@@ -683,8 +685,8 @@ double* scratch_on(int device) {
 hipError_t launch_grad_finish(const double* m_x2, int bpr_x2, const double* m_y2, int bpr_y2, const double* m_y1,
                               const double* m_x1, int nx, int ny, double gscale, double* dldv, hipStream_t s) {
     const int nxy = nx * ny;
-    hipLaunchKernelGGL(k_grad_finish, dim3(nxy / kFinishEntries), dim3(256), 0, s, m_x2, bpr_x2, m_y2, bpr_y2, m_y1,
-                       m_x1, nx, ny, gscale, dldv);
+    hipLaunchKernelGGL(k_grad_finish, dim3((nxy + kFinishEntries - 1) / kFinishEntries), dim3(256), 0, s, m_x2, bpr_x2,
+                       m_y2, bpr_y2, m_y1, m_x1, nx, ny, gscale, dldv);
     return hipGetLastError();
 }
 
