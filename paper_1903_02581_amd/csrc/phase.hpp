@@ -24,12 +24,13 @@ __host__ __device__ __forceinline__ double reduce_2pi(double th) {
 // library's sincos (which reduces any argument again), square root and division, 256x128
 // complex64 x2+V went 7.62 -> 6.09 ms and y2+V 6.91 -> 5.55, the 64x64 complex128
 // plane pass 214 -> 143 us, 96x24 complex128 x2+V 59 -> 52 us.  Past the range of reduce_2pi (|th| of about
-// 1e14, where th itself is rounded by 0.01) the result is still a unit number.
+// 1e14, where th itself is rounded by 0.01) the result is still a unit number.  An infinite or
+// NaN angle has none: it gives NaN, which the norm then shows.
 __host__ __device__ __forceinline__ double2 expmi(double th) {
     const double r = reduce_2pi(th);
     const double q = rint(r * 0.6366197723675814);  // 2 / pi
     double s = fma(-q, 6.123233995736766e-17, fma(-q, 1.5707963267948966, r));
-    s = fabs(s) < 1.0 ? s : 0.0;
+    s = fabs(s) >= 1.0 ? 0.0 : s;
     const double z = s * s;
     double ps = 2.8114572543455206e-15;   // 1 / 17!
     ps = fma(ps, z, -7.647163731819816e-13);
