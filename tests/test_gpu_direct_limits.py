@@ -1,12 +1,16 @@
 """The per-point potential factor where its angle leaves the number range: what the table form
 answers.  A softening length whose square underflows makes V12 infinite at r1 = r2, and a
 potential whose angle overflows has no phase: the state turns non-finite and the watchdog says so
-(status -6).  On the fused small-grid steps and on the line passes.
+(status -6).  A softening length whose square overflows makes V12 vanish: the run is the one
+without the two-body term.  On the fused small-grid steps and on the line passes.
+
+Tolerance of the last: the same factors in FP64 over 3 steps, 1e-13; 5e-6 in complex64 (some ten
+roundings of 2^-24 a step in either run).
 """
 import numpy as np
 import pytest
 
-from tests.gpu_util import announce
+from tests.gpu_util import announce, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +42,14 @@ def test_infinite_angles_are_reported(nx, ny, plan, precision):
     v[1, 2] = 1e308
     for mode in ("table", "direct"):
         assert run(nx, ny, plan, precision, mode, v, dt_fs=2e4, coulomb_c=0.0)[1] == -6, mode
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-13), ("mixed", 5e-6)])
+@pytest.mark.parametrize("nx,ny,plan", SIZES)
+def test_softening_past_the_number_range(nx, ny, plan, precision, tol):
+    v = np.random.default_rng(1).uniform(-2.0, 5.0, (nx, ny))
+    ref, status = run(nx, ny, plan, precision, "table", v, coulomb_c=0.0)
+    assert status == 0
+    for mode in ("table", "direct"):
+        got, status = run(nx, ny, plan, precision, mode, v, soft_nm=1e200)
+        assert status == 0 and rel_l2(got, ref) <= tol, mode
