@@ -527,42 +527,59 @@ __global__ void __launch_bounds__(plane1_threads(NX, NY, Shape<NX>::t, Shape<NY>
         const double2* kt = a.ktab + y1 * NX;  // y-major: the line's row of wave numbers
 #pragma unroll
         for (int e = 0; e < EX; ++e) kf[e] = kt[tx + TX * (e / A2) + A1 * (e % A2)];
+        // places of the thread's elements of stage A and of stage B
+        auto at_a = [&](int e) { return at((e % A1) * A2 + tx + TX * (e / A1), y1); };
+        auto at_b = [&](int e) { return at((tx + TX * (e / A2)) * A2 + e % A2, y1); };
+        // Exchange of the line's elements, in FP64 for both storage types as in the x1 line
+        // pass: complex64 moves the real parts, then the imaginary ones, through the line's own
+        // 8-byte places, so that the LDS stays what the planes take.  (Complex64 elements
+        // here round the state twice more a step: 32x24 over 20 steps 3.98e-7 off the
+        // complex128 run against 3.62e-7 so and 3.60e-7 in four passes; 19.9 and 20.1 us a step.)
+        auto exchange = [&](auto from, auto to) {
+            if constexpr (std::is_same<S, double2>::value) {
+#pragma unroll
+                for (int e = 0; e < EX; ++e) L[from(e)] = v[e];
+                wave_sync();
+#pragma unroll
+                for (int e = 0; e < EX; ++e) v[e] = L[to(e)];
+            } else {
+                double* D = reinterpret_cast<double*>(lds_raw);
+                double re[EX];
+                wave_sync();  // the places are read as complex64 before
+#pragma unroll
+                for (int e = 0; e < EX; ++e) D[from(e)] = v[e].x;
+                wave_sync();
+#pragma unroll
+                for (int e = 0; e < EX; ++e) re[e] = D[to(e)];
+                wave_sync();
+#pragma unroll
+                for (int e = 0; e < EX; ++e) D[from(e)] = v[e].y;
+                wave_sync();
+#pragma unroll
+                for (int e = 0; e < EX; ++e) v[e] = make_double2(re[e], D[to(e)]);
+            }
+        };
 #pragma unroll
         for (int jj = 0; jj < JA; ++jj) {
-            const int jc = tx + TX * jj;
 #pragma unroll
-            for (int n1 = 0; n1 < A1; ++n1) v[jj * A1 + n1] = X::get(L[at(n1 * A2 + jc, y1)]);
+            for (int n1 = 0; n1 < A1; ++n1) v[jj * A1 + n1] = X::get(L[at_a(jj * A1 + n1)]);
             dft<A1, -1>(&v[jj * A1]);
             if constexpr (A2 > 1) {
 #pragma unroll
-                for (int k1 = 1; k1 < A1; ++k1) v[jj * A1 + k1] = cmul(v[jj * A1 + k1], twx[(jc * k1) % NX]);
-#pragma unroll
-                for (int k1 = 0; k1 < A1; ++k1) L[at(k1 * A2 + jc, y1)] = X::put(v[jj * A1 + k1]);
+                for (int k1 = 1; k1 < A1; ++k1) v[jj * A1 + k1] = cmul(v[jj * A1 + k1], twx[((tx + TX * jj) * k1) % NX]);
             }
         }
         if constexpr (A2 > 1) {
-            wave_sync();
+            exchange(at_a, at_b);
 #pragma unroll
-            for (int ii = 0; ii < IB; ++ii) {
-#pragma unroll
-                for (int j = 0; j < A2; ++j) v[ii * A2 + j] = X::get(L[at((tx + TX * ii) * A2 + j, y1)]);
-                dft<A2, -1>(&v[ii * A2]);
-            }
+            for (int ii = 0; ii < IB; ++ii) dft<A2, -1>(&v[ii * A2]);
         }
 #pragma unroll
         for (int e = 0; e < EX; ++e) v[e] = cmul(v[e], kf[e]);
         if constexpr (A2 > 1) {
 #pragma unroll
-            for (int ii = 0; ii < IB; ++ii) {
-                dft<A2, 1>(&v[ii * A2]);
-#pragma unroll
-                for (int j = 0; j < A2; ++j) L[at((tx + TX * ii) * A2 + j, y1)] = X::put(v[ii * A2 + j]);
-            }
-            wave_sync();
-#pragma unroll
-            for (int jj = 0; jj < JA; ++jj)
-#pragma unroll
-                for (int k1 = 0; k1 < A1; ++k1) v[jj * A1 + k1] = X::get(L[at(k1 * A2 + tx + TX * jj, y1)]);
+            for (int ii = 0; ii < IB; ++ii) dft<A2, 1>(&v[ii * A2]);
+            exchange(at_b, at_a);
         }
 #pragma unroll
         for (int jj = 0; jj < JA; ++jj) {
