@@ -231,7 +231,7 @@ int hom4d_conditional(hom4d* h, int32_t ix2, int32_t jy2, double* out);
  * complex128.  info_out (may be NULL): host double[3] = (k0 in 1/nm, its level
  * in meV, the target level in meV).  The handle's state is not touched.  EINVAL
  * on NULL pointers, sigma_x <= 0, non-finite inputs or top not 0/1; EHIP
- * (allocates a work buffer for the call: 4 nx ny doubles, and 1.5 nx ny^2 more at
+ * (allocates a work buffer for the call: 4 nx ny doubles, and 2 nx ny^2 more at
  * ny = 256).  Synchronises. */
 int hom4d_edge_packet(hom4d* h, const double* v_col, double sigma_x_nm, double xc_nm, int32_t top,
                       double e_above_lll_mev, double* psi_out, double* info_out);
