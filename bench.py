@@ -66,11 +66,14 @@ PASS_OF_AXIS = {0: "x1", 1: "y1", 2: "x2", 3: "y2"}
 # headers whole, and the launch-planning functions of the host and launch sources
 KERNEL_SOURCES = ["paper_1903_02581_amd/csrc/axis_pass.hpp", "paper_1903_02581_amd/csrc/axis3_pass.hpp",
                   "paper_1903_02581_amd/csrc/dft_regs.hpp", "paper_1903_02581_amd/csrc/plane_pass.hpp",
+                  "paper_1903_02581_amd/csrc/plane_regs.hpp", "paper_1903_02581_amd/csrc/phase.hpp",
                   "paper_1903_02581_amd/csrc/hom4d_internal.hpp"]
 KERNEL_FUNCTIONS = [("paper_1903_02581_amd/csrc/hom4d_host.cpp", "AxisPlan plan_axis("),
                     ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t resident_blocks("),
                     ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t launch_axis("),
-                    ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t launch_plane(")]
+                    ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t launch_plane("),
+                    ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t launch_plane1("),
+                    ("paper_1903_02581_amd/csrc/hom4d_kernels.hip", "hipError_t launch_plane_regs(")]
 
 
 def _function_text(path: str, head: str) -> bytes:
@@ -104,19 +107,6 @@ def make_prop(w, precision):
     p = Propagator.from_workload(w, precision=precision, coulomb_mode=COULOMB_MODE)
     p.set_pass_plan(PLAN)
     return p
-
-
-def step_passes(p, w, precision: str, plan: int) -> int:
-    """State passes of a step as the timed region runs it.  The library names the plan whose
-    passes it times one by one; outside that, small grids take two fused passes and some
-    complex128 ones three, the plane in registers (hom4d_set_pass_plan)."""
-    if (plan == 0 and w.nx * w.ny <= 1024 and min(w.nx, w.ny) >= 8 and max(w.nx, w.ny) <= 64
-            and (w.nx, w.ny) != (64, 12)):
-        return 2
-    if (plan == 0 and precision == "fp64" and COULOMB_MODE == "table"
-            and (w.nx, w.ny) in ((128, 128), (128, 64), (64, 128))):
-        return 3
-    return p.passes_per_step
 
 
 def sbytes(precision: str) -> int:
@@ -159,6 +149,10 @@ def pass_timing(prop, w, steps, sample_every):
     three = prop.passes_per_step == 3
     label = {"x1": "x1", "y1": "y1+V" if three else "y1", "x2": "x2 (closing half)" if three else "x2+V",
              "y2": "y2+V", "plane": "plane(x2,V,y2)"}
+    if prop.step_passes == 2:  # y1 and x1 share the (x1, y1) plane pass; x1 opens each call besides
+        (sx, nx), (sy, ny) = times["x1"], times["y1"]
+        times["y1"], times["x1"] = (2.0 * sy, ny), (sx - sy, nx - ny)
+        label["y1"], label["x1"] = "plane(y1,V,x1)", "x1 (opening half)"
     return {label[k]: sec / n for k, (sec, n) in times.items()}, {label[k]: n for k, (sec, n) in times.items()}
 
 
@@ -257,7 +251,7 @@ def config_run(name, precision, steps, warmup=3, plan=None, **overrides):
     dom, rl = roofline_of(passes, launches, w.points, precision)
     out = {"workload": name + "".join(f",{k}={v}" for k, v in overrides.items()),
            "nx": w.nx, "ny": w.ny, "points": w.points, "precision": precision,
-           "steps": steps, "passes_per_step": step_passes(p, w, precision, PLAN if plan is None else plan),
+           "steps": steps, "passes_per_step": p.step_passes,
            "gp_steps_per_s": w.points * steps / sec, "ms_per_step": sec / steps * 1e3,
            "roofline": {k: rl[k] for k in ("achieved", "frac", "kernel", "avg_launch_s", "pass_seconds")}}
     out["effective_GBps"] = out["gp_steps_per_s"] * 2 * sbytes(precision) * out["passes_per_step"] / 1e9
@@ -344,7 +338,7 @@ def profile_passes(w, precision, reps):
     the state's size (the calibration of the HBM byte counters)."""
     import torch
     prop = make_prop(w, precision)
-    axes = (0, 4, 5) if prop.passes_per_step == 3 else (0, 1, 2, 3)
+    axes = {2: (4, 6), 3: (0, 4, 5), 4: (0, 1, 2, 3)}[prop.step_passes]
     for axis in axes:
         prop.run_pass(axis, reps)
     torch.cuda.synchronize()
@@ -357,8 +351,10 @@ def profile_passes(w, precision, reps):
 
 
 def _pass_of_kernel(name: str, three_pass: bool):
-    if "k_plane2" in name:
+    if "k_plane2" in name or "k_plane_regs" in name:
         return "plane(x2,V,y2)"
+    if "k_plane1" in name:
+        return "plane(y1,V,x1)"
     m = re.search(r"k_axis3?<HIP_vector_type<(?:float|double), 2u>, (\d+), ", name)
     if not m:
         return None
@@ -375,7 +371,8 @@ def ingest_counters(fetch_csv, write_csv, workload, precision, source):
     from workloads import preset
     w = preset(workload, run=0) if workload == "mid" else preset(workload)
     copy_bytes = w.points * sbytes(precision)
-    three = workload in ("mid", "diff", "tiny")
+    with open(fetch_csv) as f:
+        three = any("k_plane" in r["Kernel_Name"] for r in csv.DictReader(f))
 
     def per_kernel(path, counter):
         vals, copies = {}, []
@@ -602,7 +599,7 @@ def main():
     sec, samples = timed_run(prop, w, args.steps, args.warmup, args.sample_every)
     value = P * args.steps / sec
     final = samples[-1]
-    passes_per_step = step_passes(prop, w, args.precision, PLAN)
+    passes_per_step = prop.step_passes
     passes, launches = pass_timing(prop, w, args.steps, args.sample_every)
     dom, roofline = roofline_of(passes, launches, P, args.precision)
     roofline["traffic"] = read_traffic(args.workload, args.precision, dom)

@@ -145,10 +145,14 @@ int hom4d_store_state(hom4d* h, double* psi4d);
 
 /* Measurement: per-pass kernel timing on the stream.  enable = 1 discards
  * earlier records and brackets every pass kernel launched afterwards by a HIP
- * event pair; 0 stops recording.  hom4d_pass_times synchronises and returns,
- * per pass kind (0 x1, 1 y1, 2 x2, 3 y2, 4 the fused (x2, y2) plane pass), the
- * summed event-to-event time in ms and the number of launches (host arrays of
- * 5); reading does not reset them.  A pool of 8192 events is created at the
+ * event pair; 0 stops recording; the passes and the state's bits are the same
+ * either way.  hom4d_pass_times synchronises and returns, per pass kind (0 x1,
+ * 1 y1, 2 x2, 3 y2, 4 the fused (x2, y2) plane pass), the summed event-to-event
+ * time in ms and the number of launches (host arrays of 5); reading does not
+ * reset them.  The fused (x1, y1) plane pass of two-pass steps counts as one y1
+ * and one x1 pass, each with half of its time: where hom4d_step_passes is 2,
+ * kind 1 holds nothing else, and kind 0 the opening x1 pass of each
+ * hom4d_step call besides.  A pool of 8192 events is created at the
  * first timed launch and kept until hom4d_destroy: while timing is on, every
  * 4096 launches the stream is synchronised and the pending pairs are folded
  * into the sums, so memory stays bounded over any number of steps.  The event
@@ -282,27 +286,32 @@ int hom4d_grad_backward_noalloc(hom4d* h, const double* w_top, const double* coe
 /* Abandon an open recording. */
 int hom4d_grad_end(hom4d* h);
 
-/* Pass plan.  plan = 0 (default): where a fused kernel is built for (nx, ny)
- * and the precision, one step is three state passes -- x1 line transforms;
- * the (x2, y2) plane of each r1 with X2, V and Y2 fused; y1 line transforms
- * with V fused.  plan = 1: four per-axis passes (x1; x2 then V; y1; y2 then V).
- * Both apply the same factors in the same order (Sec. II.C Eq. (evoloperat)).
- * The reverse (adjoint) sweep always uses the per-axis passes.  On small grids
- * (nx ny <= 1024, lengths 8 to 64 but 64x12) a plan-0 step runs as two fused
- * kernels, X2 V Y2 and Y1 V X1, except in recorded complex64 runs and while pass
- * timing is on, and on complex128 128x128, 128x64 and 64x128 grids with the
- * Coulomb table X2, V and Y2 run as one pass with the plane in registers, except
- * while pass timing is on; hom4d_pass_plan and the pass kinds of
- * hom4d_pass_times keep naming the plan above.
- * hom4d_pass_plan returns the number of passes per step in use (3 or 4). */
+/* Pass plan.  plan = 0 (default): where fused kernels are built for (nx, ny)
+ * and the precision, one step is
+ *   three state passes on 48x48 and 64x64 grids, and on complex128 128x128,
+ *     128x64 and 64x128 grids with the Coulomb table -- x1 line transforms; the
+ *     (x2, y2) plane of each r1 with X2, V and Y2 fused; y1 line transforms with
+ *     V fused;
+ *   two on small grids (nx ny <= 1024, lengths 8 to 64 but 64x12) -- X2, V and Y2
+ *     on the (x2, y2) plane; Y1, V and X1 on the (x1, y1) plane; in a recorded
+ *     complex64 run three (16x16, 24x24, 32x32, 48x16, 16x48) or four;
+ *   four elsewhere, as with plan = 1: x1; x2 then V; y1; y2 then V.
+ * All apply the same factors of Sec. II.C Eq. (evoloperat).  The reverse (adjoint)
+ * sweep always uses the per-axis passes.
+ * hom4d_step_passes returns the state passes that a step takes now: 2, 3 or 4.
+ * hom4d_pass_plan returns 3 where steps run around a fused (x2, y2) plane pass
+ * (kinds x1, plane, y1 of hom4d_pass_times), else 4. */
 int hom4d_set_pass_plan(hom4d* h, int32_t plan);
 int hom4d_pass_plan(hom4d* h);
+int hom4d_step_passes(hom4d* h);
 
 /* Measurement entry point: launch one pass kernel reps times on the bound
  * state, asynchronously.  axis: 0 = x1, 1 = y1, 2 = x2 then potential factor,
  * 3 = y2 then potential factor -- the kernels of the four-pass plan (kinetic
  * factors of a full dt); 4 = the fused (x2, y2) plane pass and 5 = y1 then
- * potential factor -- the kernels of the three-pass plan (with 0).  Each
+ * potential factor -- the kernels of the three-pass plan (with 0); 6 = the fused
+ * (x1, y1) plane pass of the two-pass plan (with 4).  EINVAL for 4 and 6 where the
+ * step has no such pass.  Each
  * launch applies a unitary factor, so the state stays normalised but no
  * longer follows the step sequence; the step count is not changed. */
 int hom4d_run_pass(hom4d* h, int32_t axis, int32_t reps);

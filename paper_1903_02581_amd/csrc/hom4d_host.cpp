@@ -253,9 +253,9 @@ struct hom4d {
     // pass timing (measurement): an event pair around every pass kernel launch
     bool timing = false;
     std::vector<hipEvent_t> ev;  // pool of 2 * kEvPairs events, created at the first timed launch
-    std::vector<int> ev_kind;    // pass kind of each pending pair (0..4)
-    double ev_ms[5] = {};        // folded sums per kind
-    int64_t ev_n[5] = {};
+    std::vector<int> ev_kind;    // pass kind of each pending pair (0..kKinds - 1)
+    double ev_ms[6] = {};        // folded sums per kind
+    int64_t ev_n[6] = {};
 };
 
 namespace {
@@ -267,6 +267,7 @@ void free_events(hom4d* h) {
 }
 
 constexpr size_t kEvPairs = 4096;
+constexpr int kKinds = 6;
 
 // Wait for the pending event pairs and add their times to the per-kind sums;
 // the events are then free for reuse.
@@ -285,9 +286,9 @@ hipError_t fold_events(hom4d* h) {
 }
 
 // Launch one pass kernel; while timing is on, between an event pair of its own.
-// kind: 0 x1, 1 y1, 2 x2, 3 y2 (the axis), 4 the fused plane pass.  The pool
-// holds kEvPairs pairs; when they are all pending the stream is synchronised
-// and their times folded into the sums.
+// kind: 0 x1, 1 y1, 2 x2, 3 y2 (the axis), 4 the fused (x2, y2) plane pass in either
+// form, 5 the fused (x1, y1) one.  The pool holds kEvPairs pairs; when they are all pending
+// the stream is synchronised and their times folded into the sums.
 template <class F>
 hipError_t timed_launch(hom4d* h, int kind, F&& launch) {
     if (!h->timing) return launch();
@@ -531,7 +532,7 @@ int run_plane_regs(hom4d* h, KTab kt) {
     if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
     PassArgs a = plane_args(h, kt == KX_HALF ? h->kxt_half : h->kxt_full);  // k-major
     a.nt = h->state_bytes > (size_t(1) << 30) ? 1 : 0;  // as the line passes (run_pass)
-    HIP_TRY(launch_plane_regs(c.nx, c.ny, a, h->stream));
+    HIP_TRY(timed_launch(h, 4, [&] { return launch_plane_regs(c.nx, c.ny, a, h->stream); }));
     return sync_check(h, "plane pass in registers");
 }
 
@@ -540,19 +541,16 @@ int run_plane1(hom4d* h, KTab kt) {
     const hom4d_cfg& c = h->cfg;
     if (!h->have_v) return fail(HOM4D_ESTATE, "no potential set (hom4d_set_potential)");
     const PassArgs a = plane_args(h, kt == KX_HALF ? h->kx_half : h->kx_full);  // y-major
-    HIP_TRY(launch_plane1(c.nx, c.ny, h->mixed, a, h->stream));
+    HIP_TRY(timed_launch(h, 5, [&] { return launch_plane1(c.nx, c.ny, h->mixed, a, h->stream); }));
     return sync_check(h, "plane pass of electron 1");
 }
 
 bool use_plane(const hom4d* h) { return h->pass_plan == 0 && h->plane_built; }
 
-// Steps as the two plane passes where both are built, except while the passes are
-// timed one by one (they are reported by the kinds of the three- and four-pass
-// plans), and in a recorded complex64 run, which keeps the passes that its reverse
-// sweep undoes: there every pass rounds the state, and the fused one rounds it in other places.
-bool use_pair(const hom4d* h) {
-    return h->pass_plan == 0 && h->pair_built && !h->timing && !(h->mixed && h->rec);
-}
+// Steps as the two plane passes where both are built, except in a recorded complex64 run,
+// which keeps the passes that its reverse sweep undoes: there every pass rounds the state,
+// and on grids without a three-pass plan the fused ones round it in other places.
+bool use_pair(const hom4d* h) { return h->pass_plan == 0 && h->pair_built && !(h->mixed && h->rec); }
 
 // n whole forward steps in two passes per step:
 //   X1 | [X2, V, Y2] | [Y1, V, X1]  ...  closing X2 half.
@@ -566,10 +564,11 @@ int run_steps_pair(hom4d* h, int64_t n, const void* src, void* dst) {
     return run_pass(h, AX_X2, KX_HALF, 0, 1, nullptr, false, 0, nullptr, nullptr, dst);
 }
 
-// Steps in three passes around the register-held plane pass, with the same exceptions.
-bool use_plane_regs(const hom4d* h) {
-    return h->pass_plan == 0 && h->regs_built && !h->timing;
-}
+// Steps in three passes around the register-held plane pass.
+bool use_plane_regs(const hom4d* h) { return h->pass_plan == 0 && h->regs_built; }
+
+// A step runs around a fused (x2, y2) plane pass.
+bool plane_step(const hom4d* h) { return use_pair(h) || use_plane(h) || use_plane_regs(h); }
 
 // n whole forward steps in three passes per step:
 //   X1 | [X2, V, Y2] (plane) | [Y1, V]  ...  closing X1, X2 halves.
@@ -610,9 +609,9 @@ int run_steps(hom4d* h, int64_t n, int nst, void* lam, bool reverse, const GradC
               void* dst = nullptr) {
     if (n <= 0) return HOM4D_OK;
     if (nst == 1 && !reverse)
-        return use_pair(h)                              ? run_steps_pair(h, n, src, dst)
-               : use_plane(h) || use_plane_regs(h) ? run_steps_plane(h, n, src, dst)
-                                                        : run_steps_axis(h, n, src, dst);
+        return use_pair(h)     ? run_steps_pair(h, n, src, dst)
+               : plane_step(h) ? run_steps_plane(h, n, src, dst)
+                               : run_steps_axis(h, n, src, dst);
     // reverse (dual-state) sweep: X1 | X2 | V, Y1 | Y2, V -- the gradient marginals of each
     // potential factor are taken by the passes on either side of it
     const bool gr = nst == 2;
@@ -1302,7 +1301,7 @@ int hom4d_pass_timing(hom4d* h, int32_t enable) {
     if (enable) {
         HIP_TRY(hipStreamSynchronize(h->stream));
         h->ev_kind.clear();  // the pool of events is kept
-        for (int k = 0; k < 5; ++k) {
+        for (int k = 0; k < kKinds; ++k) {
             h->ev_ms[k] = 0.0;
             h->ev_n[k] = 0;
         }
@@ -1316,9 +1315,10 @@ int hom4d_pass_times(hom4d* h, double* ms, int64_t* count) {
     if (!ms || !count) return fail(HOM4D_EINVAL, "NULL argument");
     HIP_TRY(hipStreamSynchronize(h->stream));
     HIP_TRY(fold_events(h));
-    for (int k = 0; k < 5; ++k) {
-        ms[k] = h->ev_ms[k];
-        count[k] = h->ev_n[k];
+    for (int k = 0; k < 5; ++k) {  // the (x1, y1) plane pass: an x1 and a y1 pass of half its time each
+        const bool shared = k == AX_X1 || k == AX_Y1;
+        ms[k] = h->ev_ms[k] + (shared ? 0.5 * h->ev_ms[5] : 0.0);
+        count[k] = h->ev_n[k] + (shared ? h->ev_n[5] : 0);
     }
     return HOM4D_OK;
 }
@@ -1332,7 +1332,12 @@ int hom4d_set_pass_plan(hom4d* h, int32_t plan) {
 
 int hom4d_pass_plan(hom4d* h) {
     if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
-    return use_plane(h) ? 3 : 4;
+    return plane_step(h) ? 3 : 4;
+}
+
+int hom4d_step_passes(hom4d* h) {
+    if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
+    return use_pair(h) ? 2 : plane_step(h) ? 3 : 4;
 }
 
 int hom4d_edge_packet(hom4d* h, const double* v_col, double sigma_x_nm, double xc_nm, int32_t top,
@@ -1411,12 +1416,15 @@ int hom4d_edge_packet(hom4d* h, const double* v_col, double sigma_x_nm, double x
 
 int hom4d_run_pass(hom4d* h, int32_t axis, int32_t reps) {
     if (!h) return fail(HOM4D_EINVAL, "handle is NULL");
-    if (axis < 0 || axis > 5) return fail(HOM4D_EINVAL, "axis=%d must be 0..5", axis);
+    if (axis < 0 || axis > 6) return fail(HOM4D_EINVAL, "axis=%d must be 0..6", axis);
     if (axis >= 4) {
         if (!h->psi) return fail(HOM4D_EUNBOUND, "no state bound");
-        if (axis == 4 && !use_plane(h)) return fail(HOM4D_EINVAL, "no fused plane pass for this size/precision");
+        if ((axis == 4 && !plane_step(h)) || (axis == 6 && !use_pair(h)))
+            return fail(HOM4D_EINVAL, "no fused plane pass for this size/precision");
         for (int32_t r = 0; r < reps; ++r) {
-            int rc = axis == 4 ? run_plane(h, KX_FULL) : run_pass(h, AX_Y1, KY_FULL, 2, 1, nullptr, false, 0, nullptr);
+            int rc = axis == 6   ? run_plane1(h, KX_FULL)
+                     : axis == 5 ? run_pass(h, AX_Y1, KY_FULL, 2, 1, nullptr, false, 0, nullptr)
+                     : use_plane_regs(h) ? run_plane_regs(h, KX_FULL) : run_plane(h, KX_FULL);
             if (rc) return rc;
         }
         return HOM4D_OK;

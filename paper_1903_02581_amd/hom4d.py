@@ -33,7 +33,7 @@ EXPORTS = ["hom4d_create", "hom4d_destroy", "hom4d_validate_cfg", "hom4d_state_b
            "hom4d_set_norm_tol", "hom4d_entanglement", "hom4d_gather_slice", "hom4d_marginal",
            "hom4d_conditional", "hom4d_edge_packet", "hom4d_grad_begin",
            "hom4d_grad_backward", "hom4d_grad_backward_noalloc", "hom4d_grad_end", "hom4d_run_pass", "hom4d_set_pass_plan",
-           "hom4d_pass_plan", "hom4d_pass_timing", "hom4d_pass_times", "hom4d_strerror",
+           "hom4d_pass_plan", "hom4d_step_passes", "hom4d_pass_timing", "hom4d_pass_times", "hom4d_strerror",
            "hom4d_last_error"]
 
 
@@ -99,6 +99,7 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
         "hom4d_run_pass": ([vp, c_int32, c_int32], c_int),
         "hom4d_set_pass_plan": ([vp, c_int32], c_int),
         "hom4d_pass_plan": ([vp], c_int),
+        "hom4d_step_passes": ([vp], c_int),
         "hom4d_pass_timing": ([vp, c_int32], c_int),
         "hom4d_pass_times": ([vp, dp, POINTER(c_int64)], c_int),
         "hom4d_strerror": ([c_int], ctypes.c_char_p),
@@ -331,14 +332,23 @@ class Propagator:
         return float(loss.value), dldv, float(dldb.value)
 
     def set_pass_plan(self, plan: int):
-        """0: fused three-pass steps where built (default); 1: four per-axis passes."""
+        """0: steps in two or three fused passes where built (default); 1: four per-axis passes."""
         self._check(self.lib.hom4d_set_pass_plan(self.h, int(plan)), "set_pass_plan")
 
     @property
     def passes_per_step(self) -> int:
+        """3 where steps run around a fused (x2, y2) plane pass (the kinds of pass_times), else 4."""
         rc = self.lib.hom4d_pass_plan(self.h)
         if rc < 0:
             self._check(rc, "pass_plan")
+        return int(rc)
+
+    @property
+    def step_passes(self) -> int:
+        """State passes that a step takes now: 2, 3 or 4."""
+        rc = self.lib.hom4d_step_passes(self.h)
+        if rc < 0:
+            self._check(rc, "step_passes")
         return int(rc)
 
     PASS_KINDS = ("x1", "y1", "x2", "y2", "plane")
@@ -348,7 +358,8 @@ class Propagator:
         self._check(self.lib.hom4d_pass_timing(self.h, 1 if enable else 0), "pass_timing")
 
     def pass_times(self) -> dict:
-        """{kind: (summed seconds, launches)} of the launches recorded since pass_timing(True)."""
+        """{kind: (summed seconds, launches)} of the launches recorded since pass_timing(True); the
+        (x1, y1) plane pass of two-pass steps counts as a y1 and an x1 pass of half its time."""
         ms = np.zeros(5, dtype=np.float64)
         cnt = np.zeros(5, dtype=np.int64)
         self._check(self.lib.hom4d_pass_times(self.h, _dptr(ms), cnt.ctypes.data_as(POINTER(c_int64))),
@@ -356,7 +367,7 @@ class Propagator:
         return {k: (float(ms[i]) * 1e-3, int(cnt[i])) for i, k in enumerate(self.PASS_KINDS) if cnt[i]}
 
     def run_pass(self, axis: int, reps: int = 1):
-        """Launch one of the four fused pass kernels reps times (measurement only)."""
+        """Launch one of the pass kernels (hom4d_run_pass) reps times (measurement only)."""
         self._check(self.lib.hom4d_run_pass(self.h, int(axis), int(reps)), "run_pass")
 
     def grad_end(self):

@@ -56,7 +56,7 @@ def main(argv=None) -> int:
           "ly_nm": w.ly, "points": w.points, "precision": args.precision,
           "coulomb_mode": args.coulomb_mode, "b_tesla": w.b_tesla, "dt_fs": w.dt_fs,
           "steps": steps, "every": args.every, "sym": w.sym, "soft_nm": w.soft_nm,
-          "coulomb_c": w.coulomb_c, "passes_per_step": p.passes_per_step,
+          "coulomb_c": w.coulomb_c, "passes_per_step": p.step_passes,
           "entanglement_rows": None if args.no_entanglement else [j1, j2]})
 
     def sample(step):
