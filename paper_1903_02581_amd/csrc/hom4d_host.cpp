@@ -119,14 +119,20 @@ int64_t ilog2_pow2_divisor(int64_t v) {  // largest power of two dividing v
     return v & (-v);
 }
 
-// Lines of an x2 block: a part of one y2 row, so that its accesses are whole runs and
+// Lines of an x2 block at most: a part of one y2 row, so that its accesses are whole runs and
 // (gradient partials) its lines share r1.  Forward passes let blocks run over row ends where
 // the row's largest power of two is 4 or less, which would leave blocks of half a
-// wavefront: x2+V at 128x12 complex128 28.2 -> 21.5 us, 128x6 20.9 -> 15.7, 256x12 complex64
-// 68.6 -> 52.1; at 8 (ny = 24) it changes nothing, at 16 (64x48) 50.6 -> 52.9.
-int64_t x2_lines(int ny, bool grad) {
+// wavefront: up to a wavefront, and past it while 192 blocks (of 256 CUs) are left.  x2+V
+// against blocks inside a row: 128x12 complex128 26.0 -> 19.8 us, 128x6 18.1 -> 9.6, 96x6 16.7
+// -> 8.1, 32x4 4.1 -> 3.6, 256x12 complex64 65.8 -> 50.9; as wide as they may be on the
+// smallest grids they leave CUs idle (128x4 complex64 5.2 -> 6.8 us, with this 5.1; 48x6
+// complex128 11.4 -> 6.4 and 5.2).  At 8 (ny = 24) it changes nothing, at 16 (64x48) 50.6 -> 52.9.
+int64_t x2_lines(int ny, bool grad, int t, int64_t nlines) {
     const int64_t d = ilog2_pow2_divisor(ny);
-    return grad || d > 4 ? d : 1 << 20;
+    if (grad || d > 4) return d;
+    int64_t w = std::max<int64_t>(64 / t, d);
+    while (nlines / (2 * w) >= 192) w *= 2;
+    return w;
 }
 
 AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
@@ -158,7 +164,7 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         // x1: 0.559 -> 0.526 ms).
         int64_t w = axis3_nominal_w(axis, p.n, t3, nst, mixed);
         w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
-        if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad));
+        if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad, t3, p.nlines));
         if (axis == AX_Y2 && grad) w = std::min<int64_t>(w, ilog2_pow2_divisor(nx));
         p.W = (int)std::max<int64_t>(w, 1);
         // persistent form on the complex64 x1 pass of 128- and 256-point lines (256x128 x1
@@ -182,7 +188,7 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         while (w > cap) w >>= 1;
     }
     w = std::min<int64_t>(w, ilog2_pow2_divisor(p.nlines));
-    if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad));
+    if (axis == AX_X2) w = std::min<int64_t>(w, x2_lines(ny, grad, sh.t, p.nlines));
     if (axis == AX_Y2 && grad) w = std::min<int64_t>(w, ilog2_pow2_divisor(nx));
     if (axis == AX_Y1) w = std::min<int64_t>(w, ilog2_pow2_divisor(nxy));  // a block's lines share x1
     if (w < 1) w = 1;
