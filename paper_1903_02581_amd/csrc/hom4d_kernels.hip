@@ -285,12 +285,17 @@ __global__ void __launch_bounds__(kPairThreads) k_loss_lambda(const S* psi, S* l
 }
 
 // out[block * width + q] = sum of part[b * width + q] over the block's share of the
-// partial sums, fixed order; grid (width, blocks).
+// partial sums, fixed order; grid (width, blocks).  Bound by the latency of its loads: eight in
+// flight take the observables of 32x32 complex64 states from 29.9 to 28.5 us.
 __global__ void __launch_bounds__(256) k_reduce_parts(const double* part, int nparts, int width, double* out) {
     __shared__ double red[4];
     const int q = blockIdx.x;
     double acc = 0.0;
-    for (int b = blockIdx.y * 256 + threadIdx.x; b < nparts; b += gridDim.y * 256) acc += part[(int64_t)b * width + q];
+    const int step = gridDim.y * 256;
+    for (int b0 = blockIdx.y * 256 + threadIdx.x; b0 < nparts; b0 += 8 * step)
+        batched<8, 8>(
+            [&](int i) { return b0 + i * step < nparts ? part[(int64_t)(b0 + i * step) * width + q] : 0.0; },
+            [&](int i, double v) { acc = b0 + i * step < nparts ? acc + v : acc; });
     const double s = block_sum(acc, red);
     if (threadIdx.x == 0) out[blockIdx.y * width + q] = s;
 }
@@ -362,15 +367,26 @@ __global__ void __launch_bounds__(256) k_grad_finish(const double* m_x2, int bpr
     }
 }
 
-// Grid of a pair kernel: K accesses per thread and row where a row fills them, chunks
-// of r2 by groups of rows, about kPairBlocks blocks (fixed by the sizes alone).
+// Grid of a pair kernel: four accesses per thread and row where they fill at least two thirds
+// of their chunks of r2, one otherwise (48x48 complex64 fills 56% of two chunks: observables
+// 43 us, with one access 38; 48x24 complex128 30 and 29; at 75% four are as fast); chunks by groups
+// of rows, about kPairBlocks blocks, of the same number of rows each where that is up to
+// four (32x24 complex128: 28 -> 25.5 us).  Fixed by the sizes alone.
 template <class S>
-bool pair_k4(int nxy) { return nxy >= 4 * kPairThreads * kVec<S>; }
+int pair_chunks(int nxy, int k) {
+    const int span = k * kPairThreads * kVec<S>;
+    return (nxy + span - 1) / span;
+}
+template <class S>
+bool pair_k4(int nxy) {
+    constexpr int span = 4 * kPairThreads * kVec<S>;
+    return nxy >= span && 3 * nxy >= 2 * span * pair_chunks<S>(nxy, 4);
+}
 template <class S>
 dim3 pair_grid(int nxy) {
-    const int span = (pair_k4<S>(nxy) ? 4 : 1) * kPairThreads * kVec<S>;
-    const int chunks = (nxy + span - 1) / span;
-    return dim3(chunks, std::min(nxy, std::max(1, kPairBlocks / chunks)));
+    const int chunks = pair_chunks<S>(nxy, pair_k4<S>(nxy) ? 4 : 1);
+    const int groups = std::min(nxy, std::max(1, kPairBlocks / chunks)), rows = (nxy + groups - 1) / groups;
+    return dim3(chunks, rows <= 4 ? (nxy + rows - 1) / rows : groups);
 }
 inline int blocks_of(dim3 g) { return (int)(g.x * g.y); }
 
