@@ -21,8 +21,8 @@
 //
 // PERS (the forward complex64 x1 pass of 128- and 256-point lines): the kernel is
 // persistent: a block walks tiles of W lines (tile = blockIdx.x, + gridDim.x, ...) and
-// issues the loads of its next tile while it transforms the current one (on the nominal
-// width in four parts, from its start and between its exchanges), so that the HBM reads of
+// issues the loads of its next tile while it transforms the current one (in four parts,
+// from its start and between its exchanges), so that the HBM reads of
 // one tile overlap the arithmetic and LDS exchanges of the previous one inside the block,
 // instead of relying on other resident blocks being out of phase.  Its exchanges
 // synchronise the block on LDS alone (lds_barrier), leaving the prefetch loads and the
@@ -87,11 +87,12 @@ constexpr int axis3_min_waves(int axis, int n, int nst, bool c64) {
 
 // WC > 0: the block holds WC lines, a compile-time constant (the nominal width
 // of the pass, axis3_nominal_w), so every LDS address is a per-thread base plus
-// an immediate offset; WC = 0: a.W lines, for grids that allow fewer.
+// an immediate offset; WC = 0: a.W lines, for grids that allow fewer (never the persistent
+// pass: its ny nx ny lines and nx ny are whole blocks of 32, nx being 128 or 256).
 template <class S, int AXIS, int R1, int R2, int R3, int T, int NST, int VK, bool NT, bool PERS, int WC>
 __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value),
                                   axis3_min_waves(AXIS, R1 * R2 * R3, NST, !std::is_same<S, double2>::value)) k_axis3(const PassArgs a) {
-    static_assert(!PERS || (NST == 1 && AXIS == AX_X1 && VK == 0), "persistent: the forward x1 pass");
+    static_assert(!PERS || (NST == 1 && AXIS == AX_X1 && VK == 0 && WC > 0), "persistent: the forward x1 pass");
     // the reverse sweep (two states) applies every factor conjugated
     constexpr bool CONJ = NST == 2;
     constexpr bool SRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 0), LSRC = axis_reads_apart(AXIS, R1 * R2 * R3, NST, VK, 1);
@@ -385,98 +386,56 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
         // persistent: tiles blockIdx.x, + gridDim.x, ...; the next tile's
         // elements are loaded (as stored) before the current one is transformed
         const uint32_t ntiles = a.ntiles;
-        S raw[NST][E];
-        auto state = [&](int s) { return reinterpret_cast<S*>(s == 0 ? a.psi : a.lam); };
-        // where the states are read
-        auto from = [&](int s) {
-            if (s == 0 ? SRC : LSRC) return reinterpret_cast<const S*>(s == 0 ? a.src : a.lam_src);
-            return static_cast<const S*>(state(s));
-        };
-        double2 kreg = make_double2(0.0, 0.0);  // KROW: entry tid of the next tile's kinetic row
+        S raw[E];
+        S* const state = reinterpret_cast<S*>(a.psi);
+        const S* const from = SRC ? reinterpret_cast<const S*>(a.src) : state;  // where the state is read
+        double2 kreg = make_double2(0.0, 0.0);  // entry tid of the next tile's kinetic row
         // the kinetic row of tile tl: y1 of its lines (a tile's lines share y1)
         auto krow_of = [&](uint32_t tl) { return a.ktab + (int64_t)a.dnxy.div(tl * (uint32_t)W) * N; };
         uint32_t tile = blockIdx.x;
         if (tile < ntiles) {
             const LineGeom<AXIS> lg(a, tile * (uint32_t)W + (uint32_t)cl);
-#pragma unroll
-            for (int s = 0; s < NST; ++s)
-                walk(lg, from(s) + lg.base,
-                     [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
-            if constexpr (KROW) {
-                if (tid < N) kreg = krow_of(tile)[tid];
-            }
+            walk(lg, from + lg.base, [&](int e, const S* p) { raw[e] = ld_raw<S, NT>(p); });
+            if (tid < N) kreg = krow_of(tile)[tid];
         }
         uint32_t it = 0;  // the block's tile count: parity selects the kinetic row
-        // At the nominal width -- 1024-thread blocks, one per CU whatever their registers up to 128, at
-        // 256 points, 32-line 512-thread blocks, two per CU at up to 128 registers, at 128 --
-        // the thread's tile-invariant addresses stay in registers, and the next tile's loads
-        // are issued in parts while the current tile is transformed, instead of all at its
-        // start (the schedule below).  At other widths the thread's line slot and position
-        // index pass through an empty asm each tile, so that the LDS and table addresses derived from
-        // them are recomputed per tile rather than hoisted out of the loop and held in
-        // registers for all of it, and the loads go out at once.  256x128 x1: hoisting 5.25 ->
-        // 5.12 ms (about 8 fewer VALU instructions per point), spreading 5.10 -> 4.41 ms,
+        // The thread's tile-invariant addresses stay in registers (1024-thread blocks, one per CU
+        // whatever their registers up to 128, at 256 points; 32-line 512-thread blocks, two per
+        // CU at up to 128 registers, at 128), and the next tile's loads are issued in parts while
+        // the current tile is transformed, instead of all at its start.  256x128 x1: hoisting
+        // 5.25 -> 5.12 ms (about 8 fewer VALU instructions per point), spreading 5.10 -> 4.41 ms,
         // with fewer registers held over the tile; the 128-point pass, hoisted and spread:
         // 128x96 0.559 -> 0.526 ms, 128x64 0.279 -> 0.234 ms.
-        constexpr bool WIDE = WC > 0;
         auto one_tile = [&](uint32_t tl) {
-            if constexpr (!WIDE) asm volatile("" : "+v"(t), "+v"(cl));
             const uint32_t line = tl * (uint32_t)W + (uint32_t)cl;
             const LineGeom<AXIS> lg(a, line);
-            S* ps[NST];
+            S* const ps[1] = {state + lg.base};
 #pragma unroll
-            for (int s = 0; s < NST; ++s) ps[s] = state(s) + lg.base;
-#pragma unroll
-            for (int s = 0; s < NST; ++s)
-#pragma unroll
-                for (int e = 0; e < E; ++e) v[s][e] = widen(raw[s][e]);
-            if constexpr (KROW) {
-                // visible to every thread after the first exchange barrier; the row
-                // written two tiles ago was last read before this tile's barriers
-                double2* row = twl + N * (1 + (it & 1));
-                if (tid < N) row[tid] = kreg;
-                krow = row;
-            }
+            for (int e = 0; e < E; ++e) v[0][e] = widen(raw[e]);
+            // visible to every thread after the first exchange barrier; the row
+            // written two tiles ago was last read before this tile's barriers
+            double2* row = twl + N * (1 + (it & 1));
+            if (tid < N) row[tid] = kreg;
+            krow = row;
             const uint32_t next = tl + gridDim.x;
-            if constexpr (WIDE) {
-                const bool has_next = next < ntiles;
-                const LineGeom<AXIS> ln(a, (has_next ? next : tl) * (uint32_t)W + (uint32_t)cl);
-                const S* nbase[NST];
-#pragma unroll
-                for (int s = 0; s < NST; ++s) nbase[s] = from(s) + ln.base;
-                if constexpr (KROW) {
-                    if (has_next && tid < N) kreg = krow_of(next)[tid];
-                }
-                // NP parts of the E elements, part j issued at slot j - 1 (slot -1: before the first
-                // stage, slot k >= 0: after exchange k), the fastest of the schedules measured
-                // (after the four exchanges 4.56-4.65 ms at 256x128, three or two parts from the
-                // start 4.62 and 4.76 ms)
-                constexpr int NP = 4;
-                constexpr int PART = (E + NP - 1) / NP;
-                auto part = [&](int slot) {
-                    const int j = slot + 1;
-                    if (has_next && j >= 0 && j < NP) {
-#pragma unroll
-                        for (int s = 0; s < NST; ++s)
-                            walk_part(ln, nbase[s], j * PART, (j + 1) * PART < E ? (j + 1) * PART : E,
-                                      [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
-                    }
-                };
-                part(-1);
-                round_trip(lg, line, tl, ps, part);
-            } else {
-                if (next < ntiles) {
-                    const LineGeom<AXIS> ln(a, next * (uint32_t)W + (uint32_t)cl);
-#pragma unroll
-                    for (int s = 0; s < NST; ++s)
-                        walk(ln, from(s) + ln.base,
-                             [&](int e, const S* p) { raw[s][e] = ld_raw<S, NT>(p); });
-                    if constexpr (KROW) {
-                        if (tid < N) kreg = krow_of(next)[tid];
-                    }
-                }
-                round_trip(lg, line, tl, ps, [](int) {});
-            }
+            const bool has_next = next < ntiles;
+            const LineGeom<AXIS> ln(a, (has_next ? next : tl) * (uint32_t)W + (uint32_t)cl);
+            const S* nbase = from + ln.base;
+            if (has_next && tid < N) kreg = krow_of(next)[tid];
+            // NP parts of the E elements, part j issued at slot j - 1 (slot -1: before the first
+            // stage, slot k >= 0: after exchange k), the fastest of the schedules measured
+            // (after the four exchanges 4.56-4.65 ms at 256x128, three or two parts from the
+            // start 4.62 and 4.76 ms)
+            constexpr int NP = 4;
+            constexpr int PART = (E + NP - 1) / NP;
+            auto part = [&](int slot) {
+                const int j = slot + 1;
+                if (has_next && j >= 0 && j < NP)
+                    walk_part(ln, nbase, j * PART, (j + 1) * PART < E ? (j + 1) * PART : E,
+                              [&](int e, const S* p) { raw[e] = ld_raw<S, NT>(p); });
+            };
+            part(-1);
+            round_trip(lg, line, tl, ps, part);
             ++it;
         };
         // The first tile is peeled off the loop, so that the loop is entered, like
@@ -515,8 +474,11 @@ __global__ void __launch_bounds__(axis3_block_threads(AXIS, R1 * R2 * R3, NST, !
 template <class S, int AXIS, int R1, int R2, int R3, int T, int NST, int VK, bool NT, bool PERS>
 AxisKernel pick_w(int w) {
     constexpr int WN = axis3_nominal_w(AXIS, R1 * R2 * R3, T, NST, !std::is_same<S, double2>::value);
-    return w == WN ? k_axis3<S, AXIS, R1, R2, R3, T, NST, VK, NT, PERS, WN>
-                   : k_axis3<S, AXIS, R1, R2, R3, T, NST, VK, NT, PERS, 0>;
+    if (w == WN) return k_axis3<S, AXIS, R1, R2, R3, T, NST, VK, NT, PERS, WN>;
+    if constexpr (PERS)
+        return nullptr;
+    else
+        return k_axis3<S, AXIS, R1, R2, R3, T, NST, VK, NT, PERS, 0>;
 }
 
 template <class S, int AXIS, int NST, int VK, bool NT, bool PERS = false>

@@ -169,11 +169,10 @@ AxisPlan plan_axis(int axis, int nx, int ny, int nst, bool grad, bool mixed) {
         p.W = (int)std::max<int64_t>(w, 1);
         // persistent form on the complex64 x1 pass of 128- and 256-point lines (256x128 x1
         // 5.87 ms without, 4.45 ms with it); the other passes, the reverse x1 pass, FP64 and
-        // 96-point lines measured slower that way.  It stages each tile's kinetic row, so a
-        // tile's lines share y1 and the block's threads cover a row.
+        // 96-point lines measured slower that way.  It stages each tile's kinetic row: a
+        // tile's 32 lines share y1, since 32 divides nx ny, and its threads cover a row.
         p.pers = mixed && p.n >= 128 && axis == AX_X1 && nst == 1;
-        if (p.pers && (nxy % p.W != 0 || (int64_t)p.t * p.W < p.n)) p.pers = false;
-        p.lds = axis3_pass_lds_bytes(axis, p.n, p.W, nst, mixed, p.pers);
+        p.lds = axis3_pass_lds_bytes(p.n, p.W, nst, mixed, p.pers);
         return p;
     }
     int64_t w = 256 / sh.t;

@@ -158,7 +158,7 @@ __host__ __device__ constexpr size_t axis3_lds_bytes(int n, int w, int nst, bool
 }
 // ... of a pass: the persistent x1 pass keeps two kinetic rows after its
 // twiddles, one more row of n complex128 entries
-__host__ __device__ constexpr size_t axis3_pass_lds_bytes(int axis, int n, int w, int nst, bool c64, bool pers) {
+__host__ __device__ constexpr size_t axis3_pass_lds_bytes(int n, int w, int nst, bool c64, bool pers) {
     return axis3_lds_bytes(n, w, nst, c64) + (pers ? (size_t)n * 16u : 0u);
 }
 
