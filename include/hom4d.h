@@ -252,7 +252,12 @@ int hom4d_gather_slice(hom4d* h, const int32_t* ix1, int32_t n1, int32_t jy1,
  * the state is copied into the caller-owned device pool (pool_bytes bytes,
  * slots of hom4d_state_bytes).  hom4d_step returns ENOMEM, without stepping,
  * when a checkpoint it would reach does not fit.  EINVAL on ckpt_every < 1 or
- * a NULL pool, ENOMEM if the pool is smaller than one state. */
+ * a NULL pool, ENOMEM if the pool is smaller than one state.
+ * The state is closed at every checkpoint, and a recorded complex64 run keeps the
+ * passes that its reverse sweep undoes.  So its state has the bits of an unrecorded
+ * run with the same closings (a hom4d_step call per segment), except on grids of
+ * two-pass steps without a three-pass plan (hom4d_set_pass_plan), where the two
+ * runs round a complex64 state equally often in other places and differ by that. */
 int hom4d_grad_begin(hom4d* h, int32_t ckpt_every, void* d_pool, size_t pool_bytes);
 
 /* Reverse sweep for L = sum w_L |Psi_N|^2 with
