@@ -170,9 +170,9 @@ __device__ __forceinline__ double2 vcombine(const PassArgs& a, const VLoad& l, i
             const double ddx = (double)(i1 - i2) * a.dx;
             const double ddy = (double)(j1 - j2) * a.dy;
             const double r2 = ddx * ddx + ddy * ddy;
-            // (a softening length or box whose square is past the number range: V12 = 0)
-            const double d2 = r2 + a.soft2;
-            double vc = d2 < __builtin_inf() ? a.ck * rsqrt_of(d2) : 0.0;
+            // (a softening length or box whose square is past the number range leaves 1e-154 of C:
+            // an infinite argument would be NaN; the minimum costs one instruction, a select three)
+            double vc = a.ck * rsqrt_of(fmin(r2 + a.soft2, 1.7976931348623157e308));
             if (a.inv_screen > 0.0) vc *= exp(-sqrt(r2) * a.inv_screen);
             v += vc;
         }
