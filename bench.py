@@ -157,9 +157,10 @@ def pass_timing(prop, w, steps, sample_every):
 
 
 def roofline_of(passes, launches, points, precision):
-    """The dominant pass kernel against the HBM peak: algorithmic bytes of one launch (one
-    read and one write of every grid point) over its average launch duration."""
-    dom = max(passes, key=passes.get)
+    """The dominant pass kernel (by its time over the region) against the HBM peak:
+    algorithmic bytes of one launch (one read and one write of every grid point) over its
+    average launch duration."""
+    dom = max(passes, key=lambda k: passes[k] * launches[k])
     alg = 2 * sbytes(precision) * points
     achieved = alg / passes[dom] / 1e9
     return dom, {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
